@@ -84,7 +84,7 @@ def parse():
 # sources a committed profile depends on: the resampling kernels, or the learned cache's
 KERNEL_SOURCES = {
     "resampling": ["paper_2108_05263_amd/csrc/gi_kernels.hip", "paper_2108_05263_amd/csrc/gi_device.hpp",
-                   "include/gi.h"],
+                   "paper_2108_05263_amd/csrc/gi_lists.hpp", "include/gi.h"],
     "mlp": ["paper_2108_05263_amd/csrc/gi_mlp.hip", "paper_2108_05263_amd/csrc/gi_mlp.hpp",
             "paper_2108_05263_amd/csrc/gi_device.hpp", "include/gi.h"],
 }
@@ -431,7 +431,7 @@ def quality(gi, sg, torch, cfg, frames, n_eval, ref_spp, n_seeds):
 # --------------------------------------------------------------------------
 # rocprofv3 runs behind the committed profiles/ summaries
 # --------------------------------------------------------------------------
-PROBE_INITIAL = "k_initial<true, false, false, false, 0>"    # the probe form's initial pass (scene in LDS, FP32 texels)
+PROBE_INITIAL = "k_initial_tile<false, 0, 512, true>"    # the probe form's initial pass (FP32 texels)
 # the probe form's other resampling kernels of the 1080p workload (scene in LDS, FP32 texels)
 REUSE_KERNELS = ("k_temporal<true, false>", "k_spatial<true, false, 5>", "k_shade<true, false, false, 0>")
 SQ_SETS = {"sq1": "SQ_WAVES SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU "

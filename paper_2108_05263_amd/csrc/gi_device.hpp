@@ -59,7 +59,7 @@ __device__ __forceinline__ uint4 philox(uint64_t seed, uint32_t c0, uint32_t c1,
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
         uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
         uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-        uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+        uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96), n2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
         c0 = n0;
         c1 = lo1;
         c2 = n2;
@@ -707,90 +707,123 @@ __device__ __forceinline__ void irr_record(__amdgpu_buffer_rsrc_t r, uint32_t of
     }
 }
 
-// Per-axis quantities of the query cell's two corner layers: offsets of the
-// layers' probe coordinate from p, the trilinear fraction toward the upper
-// layer, and the probe-index step between the layers (0 on a one-probe axis).
+// Per-axis quantities of the query cell's two corner layers: offsets from the
+// layers' probe coordinate to p, the trilinear fraction toward the upper
+// layer, and the cell's lower probe index.  (pv - lo) / sp is rounded as the
+// IEEE division rounds it: r = 1/sp correctly rounded is the same for every
+// query (formed once per thread), and two residual steps from a * r give the
+// correctly rounded quotient in 5 instructions instead of the 11 of the
+// division.
 struct QueryAxis {
-    float d0, d1, fr;
-    uint32_t base, step;
+    float e0, e1, fr;
+    uint32_t b;
 };
 
-__device__ __forceinline__ QueryAxis query_axis(float pv, float lo, float sp, int na, uint32_t stride)
+__device__ __forceinline__ QueryAxis query_axis(float pv, float lo, float sp, int na)
 {
     QueryAxis q;
-    float g = (pv - lo) / sp - 0.5f;
+    const float a = pv - lo, r = 1.0f / sp;
+    float g = a * r;
+    g = fmaf(fmaf(-g, sp, a), r, g);
+    g = fmaf(fmaf(-g, sp, a), r, g) - 0.5f;
     g = fminf(fmaxf(g, 0.0f), (float)(na - 1));
-    const int b = min(max((int)floorf(g), 0), max(na - 2, 0));
-    q.fr = na >= 2 ? g - (float)b : 0.0f;
-    const int i1 = min(b + 1, na - 1);
-    q.d0 = lo + ((float)b + 0.5f) * sp - pv;
-    q.d1 = lo + ((float)i1 + 0.5f) * sp - pv;
-    q.base = (uint32_t)b * stride;
-    q.step = (uint32_t)(i1 - b) * stride;
+    q.b = min((uint32_t)g, (uint32_t)max(na - 2, 0));
+    const float fb = (float)q.b;
+    q.fr = g - fb;               // 0 on a one-probe axis (g is clamped to 0)
+    q.e0 = pv - fmaf(fb + 0.5f, sp, lo);
+    q.e1 = pv - fmaf(fb + (na >= 2 ? 1.5f : 0.5f), sp, lo);
     return q;
+}
+
+// v with its sign flipped where s is negative
+__device__ __forceinline__ float flip_sign(float v, float s)
+{
+    return __uint_as_float(__float_as_uint(v) ^ (__float_as_uint(s) & 0x80000000u));
 }
 
 // Q(p, n) = E(p, n)/pi: blend of the 8 probes of p's cell, from textures
 // of one texel format.  The per-axis terms are formed once.  The direction
 // toward p is octahedral-encoded unnormalised (the encoding divides by its
-// L1 norm).  Probe indices stay below 2^24, so byte offsets are 24-bit
-// products.  kUnroll: how many of the four (y, z) corner pairs one loop
-// iteration covers (a code-size / register trade made per kernel).
-template <int kUnroll, bool kF16>
+// L1 norm); it lies in the half-open square whose texel coordinates
+// [1/2, N + 1/2] need no clamp and truncate to their floor.  A probe sitting
+// exactly at p reads any texel: its distance is then NaN and its visibility
+// test false.  Record offsets advance by uniform steps from the cell's lower
+// corner.  kPairs: the corner pairs along x whose records are loaded together
+// (a register / latency trade made per kernel); with two, the sums over the
+// axes start from the y products, with one from the x products.
+template <int kPairs, bool kF16>
 __device__ __forceinline__ V3 probe_query_fmt(const gi_probes &pr, V3 p, V3 n)
 {
     using F = ProbeFmt<kF16>;
     const int nx = (int)pr.dims[0], ny = (int)pr.dims[1], nz = (int)pr.dims[2];
-    const QueryAxis ax = query_axis(p.x, pr.lo[0], pr.spacing[0], nx, 1u);
-    const QueryAxis ay = query_axis(p.y, pr.lo[1], pr.spacing[1], ny, (uint32_t)nx);
-    const QueryAxis az = query_axis(p.z, pr.lo[2], pr.spacing[2], nz, (uint32_t)(nx * ny));
-    const uint32_t base = ax.base + ay.base + az.base;
-    const Bilin bn = bilin(n, kIrrN);
+    const QueryAxis ax = query_axis(p.x, pr.lo[0], pr.spacing[0], nx);
+    const QueryAxis ay = query_axis(p.y, pr.lo[1], pr.spacing[1], ny);
+    const QueryAxis az = query_axis(p.z, pr.lo[2], pr.spacing[2], nz);
     const uint32_t np = (uint32_t)(nx * ny * nz);
-    const uint32_t irr_q = F::kIrrRec * (uint32_t)bn.q * np;   // slice of record q
+    const uint32_t base = __umul24(__umul24(az.b, (uint32_t)ny) + ay.b, (uint32_t)nx) + ax.b;
+    const uint32_t step_x = nx >= 2 ? 1u : 0u, step_y = ny >= 2 ? (uint32_t)nx : 0u;
+    const uint32_t step_z = nz >= 2 ? (uint32_t)(nx * ny) : 0u;
+    const Bilin bn = bilin(n, kIrrN);
+    uint32_t irr_z = F::kIrrRec * ((uint32_t)bn.q * np + base);
+    uint32_t dep_z = F::kDepProbe * base;
     const __amdgpu_buffer_rsrc_t dep_r = tex_rsrc(pr.dep, np * F::kDepProbe);
     const __amdgpu_buffer_rsrc_t irr_r = tex_rsrc(pr.irr, np * (uint32_t)kIrrQuads * F::kIrrRec);
     const float w00 = (1.0f - bn.ax) * (1.0f - bn.ay), w10 = bn.ax * (1.0f - bn.ay);
     const float w01 = (1.0f - bn.ax) * bn.ay, w11 = bn.ax * bn.ay;
     float sx = 0.0f, sy = 0.0f, sz = 0.0f, wsum = 0.0f;
-#pragma unroll kUnroll
-    for (int c = 0; c < 4; ++c) {
-        const bool oy = (c & 1) != 0, oz = (c & 2) != 0;
-        const float dy = oy ? ay.d1 : ay.d0, dz = oz ? az.d1 : az.d0;
-        const float ty = oy ? ay.fr : 1.0f - ay.fr, tz = oz ? az.fr : 1.0f - az.fr;
-        const uint32_t pyz = base + (oy ? ay.step : 0u) + (oz ? az.step : 0u);
+    float ez = az.e0, tz = 1.0f - az.fr;
+#pragma unroll 1
+    for (int oz = 0; oz < 2; ++oz) {
 #pragma unroll
-        for (int ox = 0; ox < 2; ++ox) {
-            const V3 tp = v3(ox ? ax.d1 : ax.d0, dy, dz);
-            const float tx = ox ? ax.fr : 1.0f - ax.fr;
-            const uint32_t pi = pyz + (ox ? ax.step : 0u);
-            const float r2 = dot(tp, tp);
-            const bool at_probe = !(r2 > 0.0f);
-            const float ir = frsq(r2);
-            const float r = r2 * ir;
-            const float hh = 0.5f * (1.0f + dot(n, tp) * ir);
-            // depth moments toward p (a probe sitting exactly at p reads any texel, unused)
-            const V3 dv = at_probe ? v3(0.0f, 0.0f, 1.0f) : -tp;
-            const Bilin bd = bilin(dv, kDepN);
-            float2 d[4];
-            dep_record<kF16>(dep_r, __umul24(pi, F::kDepProbe) + F::kDepRec * (uint32_t)bd.q, d);
-            float4 e0, e1, e2;
-            irr_record<kF16>(irr_r, irr_q + __umul24(pi, F::kIrrRec), e0, e1, e2);
-            const float v00 = (1.0f - bd.ax) * (1.0f - bd.ay), v10 = bd.ax * (1.0f - bd.ay);
-            const float v01 = (1.0f - bd.ax) * bd.ay, v11 = bd.ax * bd.ay;
-            const float mu = v00 * d[0].x + v10 * d[1].x + v01 * d[2].x + v11 * d[3].x;
-            const float mu2 = v00 * d[0].y + v10 * d[1].y + v01 * d[2].y + v11 * d[3].y;
-            const float var = fmaxf(fmaf(-mu, mu, mu2), pr.var_floor);
-            const float dd = r - mu;
-            const float cheb = var * rcp(fmaf(dd, dd, var));
-            const float vis = (!at_probe && r > mu) ? cheb * cheb * cheb : 1.0f;
-            const float back = at_probe ? 0.45f : hh * hh + 0.2f;
-            const float wgt = tx * ty * tz * fmaxf(back * vis, 1e-6f);
-            sx = fmaf(wgt, w00 * e0.x + w10 * e0.w + w01 * e1.z + w11 * e2.y, sx);
-            sy = fmaf(wgt, w00 * e0.y + w10 * e1.x + w01 * e1.w + w11 * e2.z, sy);
-            sz = fmaf(wgt, w00 * e0.z + w10 * e1.y + w01 * e2.x + w11 * e2.w, sz);
-            wsum += wgt;
+        for (int oy = 0; oy < 2; ++oy) {
+            const float ey = oy ? ay.e1 : ay.e0, ty = oy ? ay.fr : 1.0f - ay.fr;
+            // a layer of weight zero (p beyond the outermost probes, as next to
+            // the walls of a room) adds nothing: its records are not read
+            if (ty == 0.0f || tz == 0.0f) continue;
+#pragma unroll
+            for (int ox = 0; ox < 2; ++ox) {
+                const float ex = ox ? ax.e1 : ax.e0, tx = ox ? ax.fr : 1.0f - ax.fr;
+                const uint32_t off = (ox ? step_x : 0u) + (oy ? step_y : 0u);
+                // depth moments toward p
+                const float il = rcp(fabsf(ex) + fabsf(ey) + fabsf(ez));
+                float px = ex * il, py = ey * il;
+                const float qx = flip_sign(1.0f - fabsf(py), px), qy = flip_sign(1.0f - fabsf(px), py);
+                px = ez < 0.0f ? qx : px;
+                py = ez < 0.0f ? qy : py;
+                constexpr float hd = 0.5f * (float)kDepN;
+                const float fx = fmaf(px, hd, hd + 0.5f), fy = fmaf(py, hd, hd + 0.5f);
+                const float bx = __builtin_amdgcn_fractf(fx), by = __builtin_amdgcn_fractf(fy);
+                const uint32_t q = __umul24((uint32_t)fy, (uint32_t)(kDepN + 1)) + (uint32_t)fx;
+                float2 d[4];
+                dep_record<kF16>(dep_r, dep_z + F::kDepProbe * off + F::kDepRec * q, d);
+                float4 e0, e1, e2;
+                irr_record<kF16>(irr_r, irr_z + F::kIrrRec * off, e0, e1, e2);
+                const float xy2 = kPairs == 2 ? fmaf(ex, ex, ey * ey) : fmaf(ey, ey, ex * ex);
+                const float nxy = kPairs == 2 ? fmaf(n.x, ex, n.y * ey) : fmaf(n.y, ey, n.x * ex);
+                const float r2 = fmaf(ez, ez, xy2);
+                const float ir = frsq(r2), r = r2 * ir;
+                const float hh = 0.5f * fmaf(-fmaf(n.z, ez, nxy), ir, 1.0f);
+                const float v00 = (1.0f - bx) * (1.0f - by), v10 = bx * (1.0f - by);
+                const float v01 = (1.0f - bx) * by, v11 = bx * by;
+                const float mu = fmaf(v11, d[3].x, fmaf(v01, d[2].x, fmaf(v00, d[0].x, v10 * d[1].x)));
+                const float mu2 = fmaf(v11, d[3].y, fmaf(v01, d[2].y, fmaf(v00, d[0].y, v10 * d[1].y)));
+                const float var = fmaxf(fmaf(-mu, mu, mu2), pr.var_floor);
+                const float dd = fmaf(r2, ir, -mu);
+                const float cheb = var * rcp(fmaf(dd, dd, var));
+                const float vis = r > mu ? cheb * cheb * cheb : 1.0f;
+                const float back = r2 > 0.0f ? fmaf(hh, hh, 0.2f) : 0.45f;
+                const float tri = tx * ty * tz, bv = fmaxf(back * vis, 1e-6f), wgt = tri * bv;
+                sx = fmaf(wgt, fmaf(w11, e2.y, fmaf(w01, e1.z, fmaf(w00, e0.x, w10 * e0.w))), sx);
+                sy = fmaf(wgt, fmaf(w11, e2.z, fmaf(w01, e1.w, fmaf(w00, e0.y, w10 * e1.x))), sy);
+                sz = fmaf(wgt, fmaf(w11, e2.w, fmaf(w01, e2.x, fmaf(w00, e0.z, w10 * e1.y))), sz);
+                wsum = fmaf(tri, bv, wsum);
+            }
+            if (kPairs == 1) __builtin_amdgcn_sched_barrier(0);
         }
+        irr_z += F::kIrrRec * step_z;
+        dep_z += F::kDepProbe * step_z;
+        ez = az.e1;
+        tz = az.fr;
     }
     const float iw = rcp(wsum);
     return v3(iw * sx, iw * sy, iw * sz);

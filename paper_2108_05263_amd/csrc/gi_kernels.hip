@@ -8,11 +8,13 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <algorithm>
 #include <cstring>
 #include <type_traits>
 
 #include "gi.h"
 #include "gi_device.hpp"
+#include "gi_lists.hpp"
 #include "gi_mlp.hpp"
 
 using namespace gi;
@@ -672,6 +674,302 @@ __global__ void __launch_bounds__(kBlock, 4)
 }
 
 // --------------------------------------------------------------------------
+// initial resampling by tiles
+// --------------------------------------------------------------------------
+// The probe form without emitter candidates, one workgroup per image tile.
+// The candidate rays of all the tile's pixels are sorted by direction before
+// they are traced and shaded: a wave's 64 rays then run through the same
+// primitive lists (gi_lists.hpp) and land on the same surfaces, so its lanes
+// stay together in the walk and its probe gathers share cache lines.  The
+// RIS weights go back through LDS, where each pixel's owner streams them in
+// candidate order; a second pass evaluates the selected candidates again and
+// writes the reservoirs.  Every candidate goes through the arithmetic of
+// k_initial and the weights are summed in its order, so the results are those
+// of k_initial bit for bit.
+// Bound by vector-ALU issue (86% of its cycles at 1920x1080, M = 32) and as
+// much by the L1's return path (85%: the five 16-byte loads of a probe take
+// about 35 cycles each, one per distinct line of four lanes).  Against the
+// pixel form, M = 32: 250x141 0.795 -> 0.226 ms, 1920x1080 5.96 -> 3.23 ms,
+// with glossy layers and binary16 records 7.63 -> 5.04 ms, 3840x2160 with
+// 1024 primitives 42.7 -> 19.7 ms.  512 threads and up to 80 KB let two
+// workgroups share a CU, one tracing while the other sorts (one workgroup of
+// 1024 threads: 4.7 ms against 3.9 at 1920x1080).
+constexpr int kTileBlock = 512;
+constexpr uint32_t kTileLds = 80u * 1024u;                // LDS of a workgroup: two share a CU
+constexpr uint32_t kSortBins = 4u * kBins;
+
+// LDS after the lists: a word per ray (its sort key, then its weight), the
+// ray order, the pixels' weight sums, the cells' counts; with kPx the pixels'
+// position, normal and albedo
+__host__ __device__ constexpr uint32_t tile_bytes(uint32_t rays, uint32_t pixels, bool px)
+{
+    return rays * 6u + pixels * (px ? 40u : 4u) + (kSortBins + 8u) * 4u;
+}
+
+// minimum over a wave by DPP moves: quads, rows of 16, then row totals
+// broadcast into the next row and half (the wave's minimum ends in lane 63)
+template <int kCtrl>
+__device__ __forceinline__ float dpp_min(float v)
+{
+    const int i = __builtin_bit_cast(int, v);
+    return fminf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, kCtrl, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ float wave_min(float v)
+{
+    v = dpp_min<0xB1>(v);      // quad_perm [1, 0, 3, 2]
+    v = dpp_min<0x4E>(v);      // quad_perm [2, 3, 0, 1]
+    v = dpp_min<0x141>(v);     // row_half_mirror
+    v = dpp_min<0x140>(v);     // row_mirror
+    v = dpp_min<0x142>(v);     // row_bcast:15
+    v = dpp_min<0x143>(v);     // row_bcast:31
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
+// boxes around every thread's p and q (threads with `on` only; the boxes'
+// half extents are not >= 0 if there is none); red: 12 floats per wave.  Ends
+// with a barrier.
+template <int NT>
+__device__ __forceinline__ void block_boxes(V3 p, V3 q, bool on, float4 *red, Box3 &bp, Box3 &bq)
+{
+    const float a[12] = {p.x, p.y, p.z, -p.x, -p.y, -p.z, q.x, q.y, q.z, -q.x, -q.y, -q.z};
+    float m[12];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) m[i] = wave_min(on ? a[i] : kInf);
+    if ((threadIdx.x & 63u) == 0u)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) red[3u * (threadIdx.x >> 6) + i] = make_float4(m[4 * i], m[4 * i + 1], m[4 * i + 2], m[4 * i + 3]);
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const float4 v = red[3 * w + i];
+            m[4 * i] = fminf(m[4 * i], v.x);
+            m[4 * i + 1] = fminf(m[4 * i + 1], v.y);
+            m[4 * i + 2] = fminf(m[4 * i + 2], v.z);
+            m[4 * i + 3] = fminf(m[4 * i + 3], v.w);
+        }
+    __syncthreads();
+    const auto box = [&](const float *v) {
+        return Box3{v3(0.5f * (v[0] - v[3]), 0.5f * (v[1] - v[4]), 0.5f * (v[2] - v[5])),
+                    v3(-0.5f * (v[0] + v[3]), -0.5f * (v[1] + v[4]), -0.5f * (v[2] + v[5]))};
+    };
+    bp = box(m);
+    bq = box(m + 6);
+}
+
+// Tiles of 2^lw x 2^lh pixels (at most NT, and at most 2^16 candidates), 8x8 sub-tiles in row-major order within.
+template <bool GLOSSY, int TEX, int NT, bool PX>
+__global__ void __launch_bounds__(NT, 4)
+    k_initial_tile(gi_scene sc, gi_gbuffer gb, gi_probes pr, gi_params pp, gi_reservoirs out, float4 *resid,
+                   uint64_t seed, uint32_t frame, uint32_t lw, uint32_t lh, uint32_t C, CandWs ws, gi_mlp mlp)
+{
+    if (gated_off(ws, mlp)) return;
+    const uint32_t t = threadIdx.x, TP = 1u << (lw + lh), M = pp.M;
+    TileLists lists(gi_lds, sc.n_prims);
+    uint32_t *const word = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(gi_lds) + list_bytes(sc.n_prims));
+    float *const sum = reinterpret_cast<float *>(word + (C << (lw + lh)));
+    uint32_t *const hist = reinterpret_cast<uint32_t *>(sum + TP);
+    float *const pxd = reinterpret_cast<float *>(hist + kSortBins + 8u);
+    uint16_t *const order = reinterpret_cast<uint16_t *>(pxd + (PX ? 9u * TP : 0u));
+
+    const auto pixel_of = [&](uint32_t k, uint32_t &px, uint32_t &py) {
+        const uint32_t l = k & 63u, s = k >> 6, sw = lw > 3u ? lw - 3u : 0u;
+        const uint32_t rw = min(lw, 3u);                   // tiles below 8 pixels wide are one sub-tile
+        px = (blockIdx.x << lw) + ((s & ((1u << sw) - 1u)) << 3) + (l & ((1u << rw) - 1u));
+        py = (blockIdx.y << lh) + ((s >> sw) << 3) + (l >> rw);
+    };
+    // this thread's pixel: it generates rays of it, and owns it if t < TP
+    const uint32_t k_own = t & (TP - 1u);
+    uint32_t px, py;
+    pixel_of(k_own, px, py);
+    const uint32_t p_own = py * gb.width + px;
+    GB own{};
+    bool on = false;
+    V3 org = v3(0.0f, 0.0f, 0.0f);
+    if (px < gb.width && py < gb.height) {
+        own = load_gb<GLOSSY>(gb, p_own);
+        on = active<GLOSSY>(own);
+        org = madd(own.pos, sc.eps, own.n);
+        if (!on && t < TP) {
+            store_res(out, p_own, empty_res(0));
+            resid[p_own] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+    }
+    {
+        Box3 ob, nb;
+        // (a pixel that is nowhere does not spoil the others' box)
+        block_boxes<NT>(org, own.n, on && fabsf(org.x) + fabsf(org.y) + fabsf(org.z) < kInf, reinterpret_cast<float4 *>(word),
+                        ob, nb);
+        if (__syncthreads_or(on) == 0) return;             // no pixel of the tile is active
+        build_lists<NT>(sc, lists, ob, nb, word);          // in the rays' space
+    }
+    if (PX && t < TP) {
+        const float v[9] = {own.pos.x, own.pos.y, own.pos.z, own.n.x, own.n.y, own.n.z, own.alb.x, own.alb.y, own.alb.z};
+#pragma unroll
+        for (uint32_t c = 0; c < 9u; ++c) pxd[c * TP + t] = v[c];
+    }
+
+    const bool draws = pp.subsample <= 1u || ((uint64_t)px + py + frame) % pp.subsample == 0u;
+    const uint32_t mine = on ? (draws ? M : 1u) : 0u;      // candidates of this thread's pixel
+    const float pg = GLOSSY ? p_gloss(own.alb, own.ks) : 0.0f;
+    uint32_t chosen = ~0u;
+    float wsum = 0.0f;
+    // rounds of C candidates per pixel, then one of the selected candidates
+#pragma unroll 1
+    for (uint32_t base = 0;; base += C) {
+        const bool last = base >= M;
+        for (uint32_t b = t; b < kSortBins; b += NT) hist[b] = 0u;
+        __syncthreads();
+        // keys: the ray's cell in its list's cell, and its rank there
+        const uint32_t n_gen = last ? TP : min(C, M - base) << (lw + lh);
+        for (uint32_t e = t; e < n_gen; e += NT) {
+            const uint32_t i = last ? chosen : base + (e >> (lw + lh));
+            if (last ? i == ~0u : i >= mine) {
+                word[e] = ~0u;
+                continue;
+            }
+            const uint4 rn = philox(seed, p_own, frame, kPassInitial, i);
+            V3 w;
+            bool ok = true;
+            if (GLOSSY && pg > 0.0f && u01(rn.w) < pg) ok = ggx_sample(own.n, own.wo, own.rough, u01(rn.x), u01(rn.y), w);
+            else w = cosine_dir(own.n, u01(rn.x), u01(rn.y));
+            const uint32_t b = ok ? sort_bin_of(w) : 0u;
+            word[e] = b | (atomicAdd(&hist[b], 1u) << 16);
+        }
+        __syncthreads();
+        if (t < 64u) {
+            // first position of every cell
+            constexpr uint32_t kPer = kSortBins / 64u;
+            static_assert(kPer * 64u == kSortBins, "whole lanes");
+            uint32_t c[kPer], s = 0u;
+#pragma unroll
+            for (uint32_t q = 0; q < kPer; ++q) {
+                c[q] = hist[kPer * t + q];
+                s += c[q];
+            }
+            uint32_t a = s;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t v = __shfl_up(a, o, 64);
+                if ((int)t >= o) a += v;
+            }
+            if (t == 63u) hist[kSortBins] = a;
+            a -= s;
+#pragma unroll
+            for (uint32_t q = 0; q < kPer; ++q) {
+                hist[kPer * t + q] = a;
+                a += c[q];
+            }
+        }
+        __syncthreads();
+        for (uint32_t e = t; e < n_gen; e += NT) {
+            const uint32_t v = word[e];
+            if (v != ~0u) order[hist[v & 0xFFFFu] + (v >> 16)] = (uint16_t)(last ? (chosen << (lw + lh)) | e : e);
+        }
+        __syncthreads();
+        const uint32_t total = hist[kSortBins];
+        for (uint32_t at = t; at < total; at += NT) {
+            const uint32_t r = order[at], k = r & (TP - 1u), i = (r >> (lw + lh)) + (last ? 0u : base);
+            const uint32_t b = (word[last ? k : r] & 0xFFFFu) >> 2;
+            uint32_t qx, qy;
+            pixel_of(k, qx, qy);
+            const uint32_t p = qy * gb.width + qx;
+            GB g;
+            if constexpr (PX) {
+                g.pos = v3(pxd[k], pxd[TP + k], pxd[2u * TP + k]);
+                g.n = v3(pxd[3u * TP + k], pxd[4u * TP + k], pxd[5u * TP + k]);
+                g.alb = v3(pxd[6u * TP + k], pxd[7u * TP + k], pxd[8u * TP + k]);
+            } else {
+                g = load_gb<GLOSSY>(gb, p);
+            }
+            const V3 o = madd(g.pos, sc.eps, g.n);
+            const uint4 rn = philox(seed, p, frame, kPassInitial, i);
+            V3 w, y = v3(0.0f, 0.0f, 0.0f), ny = y, L = y, res0 = y;
+            float phat = 0.0f, wi = 0.0f;
+            uint32_t prim = GI_MISS;
+            bool dir_ok = true, lobe = false;
+            if constexpr (GLOSSY) {
+                const float pgx = p_gloss(g.alb, g.ks);
+                lobe = pgx > 0.0f && u01(rn.w) < pgx;
+                if (lobe) dir_ok = ggx_sample(g.n, g.wo, g.rough, u01(rn.x), u01(rn.y), w);
+            }
+            if (!lobe) w = cosine_dir(g.n, u01(rn.x), u01(rn.y));
+            Hit h;
+            const bool hit = dir_ok && cast_lists(sc, lists, b, o, w, h, ny);
+            if (hit) {
+                y = madd(o, h.t, w);
+                prim = h.prim;
+                const V3 v = y - g.pos;
+                const float d2 = dot(v, v);
+                const V3 wv = frsq(d2) * v;
+                const float cx = dot(g.n, wv), cy = -dot(ny, wv);
+                if (cx > 0.0f && cy > 0.0f) {
+                    if constexpr (GLOSSY) {
+                        const uint4 rg = philox(seed, p, frame, kPassGlossyCand, i);
+                        L = radiance_toward_g<TEX>(sc, pr, prim, y, ny, g.pos, u01(rg.x), u01(rg.y));
+                        const V3 f = bsdf(g.alb, g.ks, g.rough, g.n, g.wo, wv) * L;
+                        const float G = cx * cy * rcp(d2);
+                        const float pA = mix_pdf(g.alb, g.ks, g.rough, g.n, g.wo, wv) * cy * rcp(d2);
+                        phat = lum(f) * fminf(G, pp.g_max);
+                        wi = pA > 0.0f ? phat * rcp(pA) : 0.0f;
+                        if (i == 0 && G > pp.g_max && pA > 0.0f) res0 = ((G - pp.g_max) * rcp(pA)) * f;
+                    } else {
+                        L = radiance_toward<TEX == kTexF16 ? 2 : 1, TEX>(sc, pr, prim, y, ny, g.pos);
+                        const float G = cx * cy * rcp(d2);
+                        const float fl = lum((kInvPi * g.alb) * L);
+                        const float iG = rcp(G);
+                        phat = fl * fminf(G, pp.g_max);
+                        wi = kPi * phat * iG;   // p_hat / p_A with p_A = G / pi
+                        if (i == 0 && G > pp.g_max) res0 = (1.0f - pp.g_max * iG) * (g.alb * L);
+                    }
+                }
+            } else if (!GLOSSY || dir_ok) {
+                y = w;
+                L = ld3(sc.sky);
+                const float cx = dot(g.n, w);
+                if (cx > 0.0f) {
+                    if constexpr (GLOSSY) {
+                        phat = lum(bsdf(g.alb, g.ks, g.rough, g.n, g.wo, w) * L) * cx;
+                        const float pd = mix_pdf(g.alb, g.ks, g.rough, g.n, g.wo, w);
+                        wi = pd > 0.0f ? phat * rcp(pd) : 0.0f;
+                    } else {
+                        phat = lum((kInvPi * g.alb) * L) * cx;
+                        wi = kPi * phat * rcp(cx);
+                    }
+                }
+            }
+            if (!last) {
+                word[r] = __float_as_uint(wi);
+                if (i == 0u) resid[p] = make_float4(res0.x, res0.y, res0.z, 0.0f);
+            } else {
+                Res s{y, 0.0f, ny, sum[k], L, M, ((p & 0x7FFFFFu) << 9) | (i << 4) | (frame & 15u), prim};
+                s.W = phat > 0.0f ? s.wsum * rcp((float)M * phat) : 0.0f;
+                store_res(out, p, s);
+            }
+        }
+        if (last) break;
+        __syncthreads();
+        // the owners stream their candidates in order
+        if (t < TP && on) {
+            const uint32_t end = min(base + C, draws ? M : 0u);
+#pragma unroll 4
+            for (uint32_t i = base; i < end; ++i) {
+                const float wi = __uint_as_float(word[((i - base) << (lw + lh)) + t]);
+                wsum += wi;
+                if (u01(philox(seed, p_own, frame, kPassInitial, i).z) * wsum < wi) chosen = i;
+            }
+            sum[t] = wsum;
+            if (base + C >= M && chosen == ~0u) {
+                Res r = empty_res(draws ? M : 0u);
+                r.wsum = wsum;
+                store_res(out, p_own, r);
+            }
+        }
+    }
+}
+
+// --------------------------------------------------------------------------
 // reservoir merging (temporal and spatial reuse)
 // --------------------------------------------------------------------------
 struct Merge {
@@ -1316,7 +1614,74 @@ void launch_initial(bool light, bool glossy, bool f16, uint32_t lds, dim3 grid, 
     else launch_initial_l<WS, false>(glossy, f16, lds, grid, st, a...);
 }
 
+// Where k_initial_tile takes the probe form.  It needs no emitter candidates
+// and primitives that fit its lists.  A tile costs about 50 us before its
+// first ray (two share a CU) and then 1.4 us per 64 rays, the pixel form 23 us
+// per candidate while the chip is not full and 0.086 us per 1000 candidates
+// once it is (256 primitives).  So the tile form pays where a pixel takes many
+// candidates: at M = 32 from 64x36 pixels (3.0x) to 3840x2160 (2.1x).  With
+// fewer it still pays for large images, where tiles hold many rays (M = 8:
+// 1.13x at 1280x720, 1.19x at 1920x1080), and for small ones, where the pixel
+// form leaves most of the chip idle (M = 8: 1.2-1.6x up to 320x180), unless
+// the primitives outnumber a small tile's rays; in between it does not
+// (640x360: M = 8 0.75x, M = 13 0.91x), nor below M = 8.
+bool tile_form(const gi_scene *sc, const gi_params *pp, uint32_t W, uint32_t H)
+{
+    if (pp->M_light > 0u || sc->n_prims > kListMaxPrims || (sc->options & GI_OPT_NO_LDS) || pp->M < 8u) return false;
+    const uint64_t px = (uint64_t)W * H;
+    return pp->M >= 24u || px >= 900000u || (px <= 96000u && 256u * pp->M >= 3u * sc->n_prims);
+}
+
 bool glossy_scene(const gi_scene *sc) { return (sc->options & GI_OPT_GLOSSY) != 0u; }
+
+void launch_initial_tile(const gi_scene *sc, const gi_gbuffer &gb, const gi_probes &pr, const gi_params &pp,
+                         const gi_reservoirs &out, float4 *resid, uint64_t seed, uint32_t frame, const CandWs &ws,
+                         const gi_mlp &mlp, hipStream_t st)
+{
+    const uint32_t W = gb.width, H = gb.height;
+    const bool f16 = pr.texel == GI_TEXEL_F16, glossy = glossy_scene(sc);
+    // the pixels' records stay in LDS where the lists leave room for them
+    const bool px = !glossy && sc->n_prims <= 512u;
+    // The largest tile that still leaves some 1500 of them (three rounds of
+    // two workgroups per CU), down to 8x8 pixels and, for images that would
+    // not reach every CU with those, 4x4: large tiles sort more rays together
+    // and cull the scene less often, but their primitive lists are longer.
+    // 1920x1080, M = 32: 16x16 3.62 ms, 32x16 3.95, 16x8 4.35, 8x8 5.80;
+    // 3840x2160: 32x16 23.4 ms, 16x16 24.5, 16x8 29.0.
+    const auto tiles = [&](uint32_t a, uint32_t b) {
+        return (uint64_t)((W + (1u << a) - 1u) >> a) * ((H + (1u << b) - 1u) >> b);
+    };
+    uint32_t lw = pp.M <= 16u || tiles(5u, 4u) >= 8192u ? 5u : 4u, lh = 4u;
+    while (lw + lh > 6u && tiles(lw, lh) < 1500u) {
+        if (lw > lh) --lw;
+        else --lh;
+    }
+    if (tiles(3u, 3u) < 256u) lw = lh = 2u;
+    const dim3 grid((W + (1u << lw) - 1u) >> lw, (H + (1u << lh) - 1u) >> lh);
+    // candidates per round: all that leave room for two workgroups on a CU
+    const uint32_t list = list_bytes(sc->n_prims), TP = 1u << (lw + lh);
+    uint32_t C = pp.M;
+    while (C > 1u && list + tile_bytes(C * TP, TP, px) > kTileLds) C = (C + 1u) / 2u;
+    const uint32_t lds = list + std::max(tile_bytes(C * TP, TP, px), 4u * kListScratch);
+#define GI_IT(G, T, X)                                                                                       \
+    k_initial_tile<G, T, kTileBlock, X><<<grid, kTileBlock, lds, st>>>(*sc, gb, pr, pp, out, resid, seed, frame, lw, lh, C, ws, mlp)
+    if (glossy) { if (f16) GI_IT(true, kTexF16, false); else GI_IT(true, kTexF32, false); }
+    else if (px) { if (f16) GI_IT(false, kTexF16, true); else GI_IT(false, kTexF32, true); }
+    else { if (f16) GI_IT(false, kTexF16, false); else GI_IT(false, kTexF32, false); }
+#undef GI_IT
+}
+
+// the probe form of the initial pass
+void launch_initial_probe(const gi_scene *sc, const gi_gbuffer &gb, const gi_probes &pr, const gi_params &pp,
+                          const gi_reservoirs &out, float4 *resid, uint64_t seed, uint32_t frame, const CandWs &ws,
+                          const gi_mlp &mlp, hipStream_t st)
+{
+    if (tile_form(sc, &pp, gb.width, gb.height))
+        launch_initial_tile(sc, gb, pr, pp, out, resid, seed, frame, ws, mlp, st);
+    else
+        launch_initial<false>(pp.M_light > 0, glossy_scene(sc), pr.texel == GI_TEXEL_F16, initial_scene_lds(sc),
+                              tile_grid(gb.width, gb.height), st, *sc, gb, pr, pp, out, resid, seed, frame, ws, mlp);
+}
 
 #define GI_LAUNCH_LDS2(kernel, T2, grid, block, lds, stream, ...)                             \
     do {                                                                                      \
@@ -1439,10 +1804,8 @@ gi_status gi_resample_initial(const gi_scene *scene, const gi_gbuffer *gb, const
     if ((s = check_res(out, gb->width, gb->height)) != GI_OK) return s;
     if ((uint64_t)gb->width * gb->height > (1u << 23)) return GI_ERR_SHAPE;   // 23-bit tag origin
     if (gb->width == 0 || gb->height == 0) return GI_OK;
-    launch_initial<false>(params->M_light > 0, glossy_scene(scene), probes->texel == GI_TEXEL_F16, initial_scene_lds(scene),
-                          tile_grid(gb->width, gb->height), S(stream),
-                          *scene, *gb, *probes, *params, *out, reinterpret_cast<float4 *>(resid), seed, frame,
-                          CandWs{}, gi_mlp{});
+    launch_initial_probe(scene, *gb, *probes, *params, *out, reinterpret_cast<float4 *>(resid), seed, frame, CandWs{},
+                         gi_mlp{}, S(stream));
     return launched();
 }
 
@@ -1600,9 +1963,8 @@ gi_status gi_resample_initial_mlp(const gi_scene *scene, const gi_gbuffer *gb, c
     }
     if (mlp->mode != GI_MLP_ALWAYS) {
         const uint32_t gate = mlp->mode == GI_MLP_AUTO ? kRunIfProbe : kRunAlways;
-        launch_initial<false>(params->M_light > 0, false, probes->texel == GI_TEXEL_F16, initial_scene_lds(scene), tile_grid(W, H), S(stream),
-                              *scene, *gb, *probes, *params, *out, reinterpret_cast<float4 *>(resid), seed, frame,
-                              CandWs{nullptr, nullptr, nullptr, gate}, *mlp);
+        launch_initial_probe(scene, *gb, *probes, *params, *out, reinterpret_cast<float4 *>(resid), seed, frame,
+                             CandWs{nullptr, nullptr, nullptr, gate}, *mlp, S(stream));
     }
     return launched();
 }
