@@ -38,8 +38,12 @@ __device__ __forceinline__ V3 operator-(V3 a) { return v3(-a.x, -a.y, -a.z); }
 __device__ __forceinline__ V3 operator*(float s, V3 a) { return v3(s * a.x, s * a.y, s * a.z); }
 __device__ __forceinline__ V3 operator*(V3 a, V3 b) { return v3(a.x * b.x, a.y * b.y, a.z * b.z); }
 __device__ __forceinline__ float dot(V3 a, V3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
+// Sums of products that are fused here, in one fixed order: which product the
+// compiler rounds on its own depends on what surrounds the call, and kernels
+// that have to agree bit for bit would then differ.
+__device__ __forceinline__ float fdot(V3 a, V3 b) { return fmaf(a.z, b.z, fmaf(a.x, b.x, a.y * b.y)); }
 __device__ __forceinline__ V3 madd(V3 o, float t, V3 d) { return v3(fmaf(t, d.x, o.x), fmaf(t, d.y, o.y), fmaf(t, d.z, o.z)); }
-__device__ __forceinline__ float lum(V3 c) { return 0.2126f * c.x + 0.7152f * c.y + 0.0722f * c.z; }
+__device__ __forceinline__ float lum(V3 c) { return fmaf(0.0722f, c.z, fmaf(0.2126f, c.x, 0.7152f * c.y)); }
 __device__ __forceinline__ bool is_zero(V3 a) { return a.x == 0.0f && a.y == 0.0f && a.z == 0.0f; }
 __device__ __forceinline__ V3 xyz(float4 a) { return v3(a.x, a.y, a.z); }
 __device__ __forceinline__ V3 ld3(const float *a) { return v3(a[0], a[1], a[2]); }
@@ -312,6 +316,61 @@ __device__ __forceinline__ void stage_scene(const gi_scene &sc)
             mids[c] = j;
         }
         __syncthreads();
+    }
+}
+
+// The same scene in half the LDS, for workgroups that keep more in it than
+// the scene: [24 B of geometry per primitive][cell_start][items], the last two
+// as 16-bit words, an item's top bit telling a box from a sphere.
+struct GeoSmall {
+    const float2 *prims;
+    const uint16_t *cells, *items;
+    __device__ __forceinline__ explicit GeoSmall(const gi_scene &sc)
+    {
+        prims = reinterpret_cast<const float2 *>(gi_lds);
+        cells = reinterpret_cast<const uint16_t *>(prims + 3u * sc.n_prims);
+        items = cells + sc.grid_res[0] * sc.grid_res[1] * sc.grid_res[2] + 1u;
+    }
+    __device__ __forceinline__ PrimGeo geo(uint32_t i) const
+    {
+        const float2 *g = prims + 3u * (i & 0x7FFFu);
+        const float2 p = g[0], q = g[1], r = g[2];
+        const bool box = (i & 0x8000u) != 0u;
+        return PrimGeo{v3(p.x, p.y, q.x), box ? 1u : 0u, v3(q.y, r.x, r.y)};
+    }
+    __device__ __forceinline__ uint32_t cell(uint32_t c) const { return cells[c]; }
+    __device__ __forceinline__ uint32_t item(uint32_t j) const { return items[j]; }
+    __device__ __forceinline__ bool has_grid() const { return true; }
+    static constexpr bool kSplit = false;
+    __device__ __forceinline__ uint32_t mid(uint32_t) const { return 0u; }
+};
+
+// LDS bytes of the small form, or 0 for a scene it cannot hold
+__host__ __device__ __forceinline__ uint32_t lds_small_bytes(const gi_scene &sc)
+{
+    const uint64_t nc = (uint64_t)sc.grid_res[0] * sc.grid_res[1] * sc.grid_res[2];
+    if (sc.n_prims > 0x7FFFu || sc.n_items > 0xFFFFu || nc > 0xFFFFu) return 0u;
+    return (24u * sc.n_prims + 2u * ((uint32_t)nc + 1u + sc.n_items) + 15u) & ~15u;
+}
+
+// every thread of the workgroup calls it; the caller's next barrier ends it
+__device__ __forceinline__ void stage_small(const gi_scene &sc)
+{
+    const float4 *src = reinterpret_cast<const float4 *>(sc.prims);
+    float2 *geo = reinterpret_cast<float2 *>(gi_lds);
+    uint16_t *cells = reinterpret_cast<uint16_t *>(geo + 3u * sc.n_prims);
+    const uint32_t nc = sc.grid_res[0] * sc.grid_res[1] * sc.grid_res[2] + 1u, bs = blockDim.x;
+    for (uint32_t i = threadIdx.x; i < sc.n_prims; i += bs) {
+        float4 a, b;
+        geo_records(src[4u * i], src[4u * i + 1u], a, b);
+        geo[3u * i] = make_float2(a.x, a.y);
+        geo[3u * i + 1u] = make_float2(a.z, b.x);
+        geo[3u * i + 2u] = make_float2(b.y, b.z);
+    }
+    for (uint32_t i = threadIdx.x; i < nc; i += bs) cells[i] = (uint16_t)sc.cell_start[i];
+    for (uint32_t i = threadIdx.x; i < sc.n_items; i += bs) {
+        const uint32_t it = sc.cell_items[i];
+        cells[nc + i] = (uint16_t)(it | (__float_as_uint(src[4u * it].w) != 0u ? 0x8000u : 0u));
     }
 }
 
@@ -1068,13 +1127,13 @@ __device__ __forceinline__ float target(V3 x, V3 nx, V3 rho, V3 y, V3 ny, V3 L, 
 {
     float fl = kInvPi * lum(rho * L);
     if (is_zero(ny)) {
-        float cx = dot(nx, y);
+        float cx = fdot(nx, y);
         return cx > 0.0f ? fl * cx : 0.0f;
     }
     V3 v = y - x;
-    float d2 = dot(v, v);
+    float d2 = fdot(v, v);
     V3 w = frsq(d2) * v;
-    float cx = dot(nx, w), cy = -dot(ny, w);
+    float cx = fdot(nx, w), cy = -fdot(ny, w);
     if (cx <= 0.0f || cy <= 0.0f) return 0.0f;
     float G = cx * cy * rcp(d2);
     return fl * fminf(G, g_max);

@@ -25,33 +25,14 @@ constexpr int kTile = 16;
 constexpr int kBlock = 256;
 constexpr uint32_t kSelBytes = 64u;   // k_initial's per-thread slot: selected candidate (3 float4), residual
 
-// Workgroups are dealt round-robin to the chip's 8 XCDs (each with its own
-// L2).  Workgroup L runs on XCD L % 8; it is given tile (L % 8) * chunk +
-// L / 8 of the row-major tile order, so every XCD works through one
-// contiguous band of the image and its L2 sees the scene and probes that
-// band's rays reach, instead of rays from the whole frame.
-#ifndef GI_XCD_BANDS
-#define GI_XCD_BANDS 0
-#endif
+// Workgroups are dealt round-robin to the chip's 8 XCDs, each with its own L2
 constexpr uint32_t kXcds = 8;
 
 __device__ __forceinline__ bool tile_pixel(uint32_t W, uint32_t H, uint32_t &px, uint32_t &py)
 {
     uint32_t t = threadIdx.x, w = t >> 6, l = t & 63u;
-    uint32_t tx, ty;
-#if GI_XCD_BANDS
-    uint32_t tiles_x = (W + kTile - 1) / kTile, tiles = tiles_x * ((H + kTile - 1) / kTile);
-    uint32_t chunk = (tiles + kXcds - 1) / kXcds;
-    uint32_t tile = (blockIdx.x % kXcds) * chunk + blockIdx.x / kXcds;
-    if (tile >= tiles) return false;
-    tx = tile % tiles_x;
-    ty = tile / tiles_x;
-#else
-    tx = blockIdx.x;
-    ty = blockIdx.y;
-#endif
-    px = tx * kTile + (w & 1u) * 8u + (l & 7u);
-    py = ty * kTile + (w >> 1) * 8u + (l >> 3);
+    px = blockIdx.x * kTile + (w & 1u) * 8u + (l & 7u);
+    py = blockIdx.y * kTile + (w >> 1) * 8u + (l >> 3);
     return px < W && py < H;
 }
 
@@ -60,47 +41,31 @@ __device__ __forceinline__ bool tile_pixel(uint32_t W, uint32_t H, uint32_t &px,
 // are mostly read through one XCD's L2.  Workgroup L runs on XCD L % 8 and
 // takes tile L / 8 (row-major) of stripe L % 8, a band of ceil(tx / 8) tile
 // columns.
-#ifndef GI_XCD_STRIPES
-#define GI_XCD_STRIPES 1
-#endif
-__device__ __forceinline__ bool tile_pixel_striped(uint32_t W, uint32_t H, uint32_t &px, uint32_t &py)
+// Tiles of SW x 16 pixels, one of t's lanes each.
+template <uint32_t SW>
+__device__ __forceinline__ bool tile_pixel_striped(uint32_t W, uint32_t H, uint32_t &px, uint32_t &py, uint32_t t)
 {
-#if GI_XCD_STRIPES
-    const uint32_t t = threadIdx.x, w = t >> 6, l = t & 63u;
-    const uint32_t tiles_x = (W + kTile - 1) / kTile;
+    const uint32_t w = t >> 6, l = t & 63u;
+    const uint32_t tiles_x = (W + SW - 1) / SW;
     const uint32_t sw = (tiles_x + kXcds - 1) / kXcds;
     const uint32_t xcd = blockIdx.x % kXcds, m = blockIdx.x / kXcds;
     const uint32_t tx = xcd * sw + m % sw, ty = m / sw;
-    px = tx * kTile + (w & 1u) * 8u + (l & 7u);
-    py = ty * kTile + (w >> 1) * 8u + (l >> 3);
+    px = tx * SW + (w % (SW / 8u)) * 8u + (l & 7u);
+    py = ty * kTile + (w / (SW / 8u)) * 8u + (l >> 3);
     return tx < tiles_x && px < W && py < H;
-#else
-    return tile_pixel(W, H, px, py);
-#endif
 }
 
-dim3 tile_grid(uint32_t W, uint32_t H);
-
-dim3 striped_grid(uint32_t W, uint32_t H)
+dim3 striped_grid(uint32_t W, uint32_t H, uint32_t SW)
 {
-#if GI_XCD_STRIPES
-    const uint32_t tx = (W + kTile - 1) / kTile, ty = (H + kTile - 1) / kTile;
+    const uint32_t tx = (W + SW - 1) / SW, ty = (H + kTile - 1) / kTile;
     const uint32_t sw = (tx + kXcds - 1) / kXcds;
     return dim3(kXcds * sw * ty);
-#else
-    return tile_grid(W, H);
-#endif
 }
 
 dim3 tile_grid(uint32_t W, uint32_t H)
 {
     uint32_t tx = (W + kTile - 1) / kTile, ty = (H + kTile - 1) / kTile;
-#if GI_XCD_BANDS
-    uint32_t chunk = (tx * ty + kXcds - 1) / kXcds;
-    return dim3(chunk * kXcds);
-#else
     return dim3(tx, ty);
-#endif
 }
 
 struct GB {
@@ -758,6 +723,33 @@ __device__ __forceinline__ void block_boxes(V3 p, V3 q, bool on, float4 *red, Bo
     bq = box(m + 6);
 }
 
+// counts -> first positions of kCells cells, the total behind them (one wave)
+template <uint32_t kCells>
+__device__ __forceinline__ void bin_starts(uint32_t *hist)
+{
+    constexpr uint32_t kPer = (kCells + 63u) / 64u;
+    const uint32_t l = threadIdx.x & 63u;
+    uint32_t c[kPer], s = 0u;
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        c[q] = kPer * l + q < kCells ? hist[kPer * l + q] : 0u;
+        s += c[q];
+    }
+    uint32_t a = s;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = __shfl_up(a, o, 64);
+        if ((int)l >= o) a += v;
+    }
+    if (l == 63u) hist[kCells] = a;
+    a -= s;
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        if (kPer * l + q < kCells) hist[kPer * l + q] = a;
+        a += c[q];
+    }
+}
+
 // Tiles of 2^lw x 2^lh pixels (at most NT, and at most 2^16 candidates), 8x8 sub-tiles in row-major order within.
 template <bool GLOSSY, int TEX, int NT, bool PX>
 __global__ void __launch_bounds__(NT, 4)
@@ -838,30 +830,7 @@ __global__ void __launch_bounds__(NT, 4)
             word[e] = b | (atomicAdd(&hist[b], 1u) << 16);
         }
         __syncthreads();
-        if (t < 64u) {
-            // first position of every cell
-            constexpr uint32_t kPer = kSortBins / 64u;
-            static_assert(kPer * 64u == kSortBins, "whole lanes");
-            uint32_t c[kPer], s = 0u;
-#pragma unroll
-            for (uint32_t q = 0; q < kPer; ++q) {
-                c[q] = hist[kPer * t + q];
-                s += c[q];
-            }
-            uint32_t a = s;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t v = __shfl_up(a, o, 64);
-                if ((int)t >= o) a += v;
-            }
-            if (t == 63u) hist[kSortBins] = a;
-            a -= s;
-#pragma unroll
-            for (uint32_t q = 0; q < kPer; ++q) {
-                hist[kPer * t + q] = a;
-                a += c[q];
-            }
-        }
+        if (t < 64u) bin_starts<kSortBins>(hist);
         __syncthreads();
         for (uint32_t e = t; e < n_gen; e += NT) {
             const uint32_t v = word[e];
@@ -1051,9 +1020,8 @@ __device__ __forceinline__ int reproject(const gi_camera &c, V3 x)
     return (int)fy * (int)c.width + (int)fx;
 }
 
-// 8 and 5 waves per SIMD for the reuse passes (4 for the glossy spatial
-// pass, whose extra state would spill more): their latency-bound gathers
-// and walks gain more from occupancy than they lose to a few spilled values
+// 8 waves per SIMD: the latency-bound gathers and walks gain more from
+// occupancy than they lose to a few spilled values
 template <bool LDS, bool GLOSSY>
 __global__ void __launch_bounds__(kBlock, 8)
     k_temporal(gi_scene sc, gi_gbuffer gb, gi_gbuffer gbp, gi_camera cam_prev, gi_reservoirs cur,
@@ -1092,86 +1060,175 @@ __global__ void __launch_bounds__(kBlock, 8)
     store_res(out, p, finish<GLOSSY>(sc, acc, m, g, Mdom, [&](int) { return load_gb<GLOSSY>(gbp, qprev); }, pp));
 }
 
+// The visibility rays of a workgroup's pixels: up to KM + 1 of each, sorted
+// by direction cell, so that all lanes of a wave walk and walk together.
+template <int KM, int NT>
+struct RayPool {
+    uint32_t q[KM][NT];                  // the domains' pixels
+    uint32_t seen[NT];                   // bit j: domain j sees the pixel's sample
+    uint32_t hist[kBins + 8];
+    uint16_t order[(KM + 1) * NT];
+};
+
 // Neighbour slots are static (KM of them, KM >= k): a slot that draws no
 // pixel (off-screen, the pixel itself, j >= k) points at the pixel itself,
 // so every neighbour load is in bounds and unconditional, and the loads of
 // all slots can be in flight together instead of one neighbour after the
-// other (the pass is bound by the latency of these gathers).
-#ifndef GI_SPATIAL_WAVES
-#define GI_SPATIAL_WAVES 5
-#endif
-template <bool LDS, bool GLOSSY, int KM>
-__global__ void __launch_bounds__(kBlock, GLOSSY ? 4 : GI_SPATIAL_WAVES)
+// other.
+// The visibility rays of all pixels go into one pool, sorted by direction
+// (about 5 per pixel at k = 5): cast pixel by pixel they kept 24 of a wave's
+// 64 lanes busy.  They are two thirds of the pass and bound it by vector-ALU
+// issue; 0.86 -> 0.59 ms at 1920x1080, 5.86 -> 2.87 ms at 3840x2160 (k = 5).
+// The rays that only decide Z are cast whether or not x sees the sample; W is
+// zero if it does not.  74 VGPRs, 5 waves per SIMD (4 with glossy layers, 6
+// for the 768-thread tiles).
+template <bool LDS, bool GLOSSY, int KM, uint32_t SW>
+__global__ void __launch_bounds__(SW * kTile, SW == 16u ? (GLOSSY ? 4 : 5) : 6)
     k_spatial(gi_scene sc, gi_gbuffer gb, gi_reservoirs in, gi_params pp, uint32_t pass, gi_reservoirs out,
               uint64_t seed, uint32_t frame)
 {
-    using Acc = typename std::conditional<LDS, GeoLds, GeoGlobal>::type;
+    constexpr int NT = (int)SW * kTile;
+    using Acc = typename std::conditional<LDS, GeoSmall, GeoGlobal>::type;
     uint32_t px, py;
-    const bool inside = tile_pixel_striped(gb.width, gb.height, px, py);
-    if (LDS) stage_scene(sc);
-    if (!inside) return;
+    const bool inside = tile_pixel_striped<SW>(gb.width, gb.height, px, py, threadIdx.x);
+    if (LDS) stage_small(sc);
     const Acc acc(sc);
-    const uint32_t W = gb.width, H = gb.height;
+    const uint32_t W = gb.width, H = gb.height, t = threadIdx.x;
     const uint32_t p = py * W + px;
-    const GB g = load_gb<GLOSSY>(gb, p);
-    const Res rc = load_res(in, p);
-    if (!active<GLOSSY>(g)) {
-        store_res(out, p, rc);
-        return;
-    }
-    // neighbour pixels: uniform in the disk (counter (pixel, frame, 2+pass, j))
-    uint32_t qidx[KM + 1];
-    bool drawn[KM];
-    float uq[KM];
-    qidx[0] = p;
+    char *const lds = reinterpret_cast<char *>(gi_lds) + (LDS ? lds_small_bytes(sc) : 0u);
+    RayPool<KM, NT> &pool = *reinterpret_cast<RayPool<KM, NT> *>(lds);
+    if (t < kBins) pool.hist[t] = 0u;
+    pool.seen[t] = 0u;
+
+    float ph = 0.0f, wsum = 0.0f;
+    uint32_t Msum = 0u;
+    bool have = false;
+    uint32_t key[KM + 1], Mdom[KM + 1];
 #pragma unroll
-    for (int j = 0; j < KM; ++j) {
-        qidx[j + 1] = p;
-        drawn[j] = false;
-        uq[j] = 0.0f;
-        if ((uint32_t)j >= pp.k) continue;
-        const uint4 rn = philox(seed, p, frame, kPassSpatial0 + pass, (uint32_t)j);
-        const float rad = pp.radius * fsqrt(u01(rn.x));
-        const float s_ = sin_rev(u01(rn.y)), c_ = cos_rev(u01(rn.y));
-        const int qx = (int)px + (int)floorf(rad * c_ + 0.5f);
-        const int qy = (int)py + (int)floorf(rad * s_ + 0.5f);
-        uq[j] = u01(rn.z);
-        if (qx < 0 || qy < 0 || qx >= (int)W || qy >= (int)H) continue;
-        if (qx == (int)px && qy == (int)py) continue;
-        drawn[j] = true;
-        qidx[j + 1] = (uint32_t)qy * W + (uint32_t)qx;
+    for (int j = 0; j <= KM; ++j) {
+        key[j] = ~0u;
+        Mdom[j] = 0u;
     }
-    // geometric validation of every drawn neighbour (its normal and depth)
-    bool use[KM];
-#pragma unroll
-    for (int j = 0; j < KM; ++j) {
-        const uint32_t q = qidx[j + 1];
-        const float4 a = reinterpret_cast<const float4 *>(gb.pos_depth)[q];
-        GB gq;
-        gq.depth = a.w;
-        if (gb.format == GI_GB_F16) {
-            const GB full = load_gb<false>(gb, q);
-            gq.n = full.n;
-            gq.prim = full.prim;
-        } else {
-            const float4 b = reinterpret_cast<const float4 *>(gb.nrm_prim)[q];
-            gq.n = xyz(b);
-            gq.prim = __float_as_uint(b.w);
+    __syncthreads();
+    const auto merge = [&] {
+        const GB g = load_gb<GLOSSY>(gb, p);
+        const Res rc = load_res(in, p);
+        if (!active<GLOSSY>(g)) {
+            store_res(out, p, rc);
+            return;
         }
-        use[j] = drawn[j] && similar(g, gq, pp);
-    }
-    // merge the pixel's own reservoir, then the neighbours in order
-    Merge m{0.0f, 0u, false, rc};
-    uint32_t Mdom[KM + 1];
-    Mdom[0] = rc.M;
-    merge_in<GLOSSY>(m, g, rc, rc.M, 0.0f, pp.g_max);
+        // neighbour pixels: uniform in the disk (counter (pixel, frame, 2+pass, j))
+        uint32_t qidx[KM + 1];
+        bool drawn[KM];
+        float uq[KM];
+        qidx[0] = p;
 #pragma unroll
-    for (int j = 0; j < KM; ++j) {
-        const Res rq = load_res(in, qidx[j + 1]);
-        Mdom[j + 1] = use[j] ? rq.M : 0u;
-        if (use[j]) merge_in<GLOSSY>(m, g, rq, rq.M, uq[j], pp.g_max);
+        for (int j = 0; j < KM; ++j) {
+            qidx[j + 1] = p;
+            drawn[j] = false;
+            uq[j] = 0.0f;
+            if ((uint32_t)j >= pp.k) continue;
+            const uint4 rn = philox(seed, p, frame, kPassSpatial0 + pass, (uint32_t)j);
+            const float rad = pp.radius * fsqrt(u01(rn.x));
+            const float s_ = sin_rev(u01(rn.y)), c_ = cos_rev(u01(rn.y));
+            const int qx = (int)px + (int)floorf(rad * c_ + 0.5f);
+            const int qy = (int)py + (int)floorf(rad * s_ + 0.5f);
+            uq[j] = u01(rn.z);
+            if (qx < 0 || qy < 0 || qx >= (int)W || qy >= (int)H) continue;
+            if (qx == (int)px && qy == (int)py) continue;
+            drawn[j] = true;
+            qidx[j + 1] = (uint32_t)qy * W + (uint32_t)qx;
+        }
+        // geometric validation of every drawn neighbour (its normal and depth)
+        bool use[KM];
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+            const uint32_t q = qidx[j + 1];
+            const float4 a = reinterpret_cast<const float4 *>(gb.pos_depth)[q];
+            GB gq;
+            gq.depth = a.w;
+            if (gb.format == GI_GB_F16) {
+                const GB full = load_gb<false>(gb, q);
+                gq.n = full.n;
+                gq.prim = full.prim;
+            } else {
+                const float4 b = reinterpret_cast<const float4 *>(gb.nrm_prim)[q];
+                gq.n = xyz(b);
+                gq.prim = __float_as_uint(b.w);
+            }
+            use[j] = drawn[j] && similar(g, gq, pp);
+        }
+        // merge the pixel's own reservoir, then the neighbours in order
+        Merge m{0.0f, 0u, false, rc};
+        Mdom[0] = rc.M;
+        merge_in<GLOSSY>(m, g, rc, rc.M, 0.0f, pp.g_max);
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+            const Res rq = load_res(in, qidx[j + 1]);
+            Mdom[j + 1] = use[j] ? rq.M : 0u;
+            if (use[j]) merge_in<GLOSSY>(m, g, rq, rq.M, uq[j], pp.g_max);
+        }
+        wsum = m.wsum;
+        Msum = m.Msum;
+        have = m.have;
+        if (!have) {
+            Res e = empty_res(Msum);
+            e.wsum = wsum;
+            store_res(out, p, e);
+        } else {
+            const Res &r = m.sel;
+            ph = res_target<GLOSSY>(g, r, pp.g_max);
+            reinterpret_cast<float4 *>(out.y_W)[p] = make_float4(r.y.x, r.y.y, r.y.z, 0.0f);
+            reinterpret_cast<float4 *>(out.n_wsum)[p] = make_float4(r.n.x, r.n.y, r.n.z, wsum);
+            reinterpret_cast<float4 *>(out.L_M)[p] = make_float4(r.L.x, r.L.y, r.L.z, __uint_as_float(Msum));
+            reinterpret_cast<uint2 *>(out.tag_prim)[p] = make_uint2(r.tag, r.prim);
+            // the visibility rays: x's own, then those of the domains whose target supports y
+            if (pp.unbiased && ph > 0.0f) {
+#pragma unroll
+                for (int j = 0; j <= KM; ++j) {
+                    if (j > 0 && Mdom[j] == 0u) continue;
+                    const GB q = j == 0 ? g : load_gb<GLOSSY>(gb, qidx[j]);
+                    if (j > 0 && res_target<GLOSSY>(q, r, pp.g_max) <= 0.0f) continue;
+                    if (j > 0) pool.q[j - 1][t] = qidx[j];
+                    const uint32_t b = sort_bin_of(is_zero(r.n) ? r.y : r.y - q.pos) >> 2;
+                    key[j] = b | (atomicAdd(&pool.hist[b], 1u) << 16);
+                }
+            }
+        }
+    };
+    if (inside) merge();
+    __syncthreads();
+    if (t < 64u) bin_starts<kBins>(pool.hist);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j <= KM; ++j)
+        if (key[j] != ~0u) pool.order[pool.hist[key[j] & 0xFFFFu] + (key[j] >> 16)] = (uint16_t)((j << 12) | t);
+    __syncthreads();
+    for (uint32_t at = t; at < pool.hist[kBins]; at += NT) {
+        const uint32_t e = pool.order[at], k = e & 0xFFFu, j = e >> 12;
+        uint32_t kx, ky;
+        tile_pixel_striped<SW>(W, H, kx, ky, k);
+        const uint32_t pk = ky * W + kx, q = j == 0u ? pk : pool.q[j - 1u][k];
+        const GB d = load_gb<false>(gb, q);
+        // the sample as its pixel has written it (the barriers order this
+        // workgroup's writes before its reads)
+        const V3 y = xyz(reinterpret_cast<const float4 *>(out.y_W)[pk]), n = xyz(reinterpret_cast<const float4 *>(out.n_wsum)[pk]);
+        if (visible(sc, acc, d.pos, d.n, y, n, is_zero(n))) atomicOr(&pool.seen[k], 1u << j);
     }
-    store_res(out, p, finish<GLOSSY>(sc, acc, m, g, Mdom, [&](int j) { return load_gb<GLOSSY>(gb, qidx[j]); }, pp));
+    __syncthreads();
+    if (!have) return;
+    // W is zero unless x sees y and p_hat(y) > 0
+    float Wt = 0.0f;
+    if (pp.unbiased) {
+        const uint32_t seen = pool.seen[t];
+        uint32_t z = Mdom[0];                 // the target at x supports y (it was chosen)
+#pragma unroll
+        for (int j = 1; j <= KM; ++j) z += (seen >> j) & 1u ? Mdom[j] : 0u;
+        if ((seen & 1u) && z > 0u) Wt = wsum * rcp((float)z * ph);
+    } else if (Msum > 0u && ph > 0.0f) {
+        Wt = wsum * rcp((float)Msum * ph);
+    }
+    out.y_W[4u * (size_t)p + 3u] = Wt;
 }
 
 // --------------------------------------------------------------------------
@@ -1689,17 +1746,32 @@ void launch_initial_probe(const gi_scene *sc, const gi_gbuffer &gb, const gi_pro
         else kernel<false, T2><<<(grid), (block), 0, (stream)>>>(__VA_ARGS__);               \
     } while (0)
 
-// kernel<LDS, GLOSSY> with both chosen at run time
-template <int KM, class... A>
-void launch_spatial(bool glossy, uint32_t lds, dim3 grid, hipStream_t st, A... a)
+template <int KM, uint32_t SW, class... A>
+void launch_spatial_t(const gi_scene *sc, uint32_t lds, uint32_t W, uint32_t H, hipStream_t st, A... a)
 {
-    if (glossy) {
-        if (lds) k_spatial<true, true, KM><<<grid, kBlock, lds, st>>>(a...);
-        else k_spatial<false, true, KM><<<grid, kBlock, 0, st>>>(a...);
+    const uint32_t bytes = lds + (uint32_t)sizeof(RayPool<KM, (int)SW * kTile>), nt = SW * kTile;
+    const dim3 grid = striped_grid(W, H, SW);
+    if (glossy_scene(sc)) {
+        if (lds) k_spatial<true, true, KM, SW><<<grid, nt, bytes, st>>>(a...);
+        else if constexpr (SW == 16u) k_spatial<false, true, KM, SW><<<grid, nt, bytes, st>>>(a...);
     } else {
-        if (lds) k_spatial<true, false, KM><<<grid, kBlock, lds, st>>>(a...);
-        else k_spatial<false, false, KM><<<grid, kBlock, 0, st>>>(a...);
+        if (lds) k_spatial<true, false, KM, SW><<<grid, nt, bytes, st>>>(a...);
+        else if constexpr (SW == 16u) k_spatial<false, false, KM, SW><<<grid, nt, bytes, st>>>(a...);
     }
+}
+
+// The scene in LDS where that leaves four workgroups of 256 threads on a CU
+// (1920x1080, 256 primitives: 0.59 ms, from global memory 0.88); a larger one
+// is shared by the 768 threads of a 48x16 tile, two of which fill a CU
+// (3840x2160, 1024 primitives: 2.87 ms, from global memory 3.76, shared by
+// 256 threads 5.18, by 512 3.85).
+template <int KM, class... A>
+void launch_spatial(const gi_scene *sc, uint32_t W, uint32_t H, hipStream_t st, A... a)
+{
+    const uint32_t lds = sc->cell_start && sc->n_items && !(sc->options & GI_OPT_NO_LDS) ? lds_small_bytes(*sc) : 0u;
+    if (lds && lds + sizeof(RayPool<KM, 256>) <= kLdsScene) launch_spatial_t<KM, 16u>(sc, lds, W, H, st, a...);
+    else if (lds && lds + sizeof(RayPool<KM, 768>) <= kTileLds) launch_spatial_t<KM, 48u>(sc, lds, W, H, st, a...);
+    else launch_spatial_t<KM, 16u>(sc, 0u, W, H, st, a...);
 }
 
 #define GI_LAUNCH_LDS_G(kernel, glossy, grid, block, lds, stream, ...)                          \
@@ -1854,11 +1926,10 @@ gi_status gi_resample_spatial(const gi_scene *scene, const gi_gbuffer *gb, const
     if (W == 0 || H == 0) return GI_OK;
     // neighbour slots: 5 (the workloads' k) or GI_MAX_K
     if (params->k <= 5u)
-        launch_spatial<5>(glossy_scene(scene), scene_lds(scene), striped_grid(W, H), S(stream), *scene, *gb, *in,
-                          *params, pass, *out, seed, frame);
+        launch_spatial<5>(scene, W, H, S(stream), *scene, *gb, *in, *params, pass, *out, seed, frame);
     else
-        launch_spatial<(int)GI_MAX_K>(glossy_scene(scene), scene_lds(scene), striped_grid(W, H), S(stream), *scene,
-                                      *gb, *in, *params, pass, *out, seed, frame);
+        launch_spatial<(int)GI_MAX_K>(scene, W, H, S(stream), *scene, *gb, *in, *params, pass, *out, seed,
+                                      frame);
     return launched();
 }
 
