@@ -750,7 +750,16 @@ __device__ __forceinline__ void bin_starts(uint32_t *hist)
     }
 }
 
-// Tiles of 2^lw x 2^lh pixels (at most NT, and at most 2^16 candidates), 8x8 sub-tiles in row-major order within.
+// pixel k of a tile of 2^lw x 2^lh pixels: 8x8 sub-tiles in row-major order
+// (tiles below 8 pixels wide are one sub-tile)
+__device__ __forceinline__ void tile_pixel_of(uint32_t k, uint32_t lw, uint32_t lh, uint32_t &px, uint32_t &py)
+{
+    const uint32_t l = k & 63u, s = k >> 6, sw = lw > 3u ? lw - 3u : 0u, rw = min(lw, 3u);
+    px = (blockIdx.x << lw) + ((s & ((1u << sw) - 1u)) << 3) + (l & ((1u << rw) - 1u));
+    py = (blockIdx.y << lh) + ((s >> sw) << 3) + (l >> rw);
+}
+
+// Tiles of 2^lw x 2^lh pixels (at most NT, and at most 2^16 candidates).
 template <bool GLOSSY, int TEX, int NT, bool PX>
 __global__ void __launch_bounds__(NT, 4)
     k_initial_tile(gi_scene sc, gi_gbuffer gb, gi_probes pr, gi_params pp, gi_reservoirs out, float4 *resid,
@@ -765,12 +774,7 @@ __global__ void __launch_bounds__(NT, 4)
     float *const pxd = reinterpret_cast<float *>(hist + kSortBins + 8u);
     uint16_t *const order = reinterpret_cast<uint16_t *>(pxd + (PX ? 9u * TP : 0u));
 
-    const auto pixel_of = [&](uint32_t k, uint32_t &px, uint32_t &py) {
-        const uint32_t l = k & 63u, s = k >> 6, sw = lw > 3u ? lw - 3u : 0u;
-        const uint32_t rw = min(lw, 3u);                   // tiles below 8 pixels wide are one sub-tile
-        px = (blockIdx.x << lw) + ((s & ((1u << sw) - 1u)) << 3) + (l & ((1u << rw) - 1u));
-        py = (blockIdx.y << lh) + ((s >> sw) << 3) + (l >> rw);
-    };
+    const auto pixel_of = [&](uint32_t k, uint32_t &px, uint32_t &py) { tile_pixel_of(k, lw, lh, px, py); };
     // this thread's pixel: it generates rays of it, and owns it if t < TP
     const uint32_t k_own = t & (TP - 1u);
     uint32_t px, py;
@@ -865,8 +869,10 @@ __global__ void __launch_bounds__(NT, 4)
             }
             if (!lobe) w = cosine_dir(g.n, u01(rn.x), u01(rn.y));
             Hit h;
-            const bool hit = dir_ok && cast_lists(sc, lists, b, o, w, h, ny);
+            uint32_t slot;
+            const bool hit = dir_ok && cast_lists(sc, lists, b, o, w, h, slot);
             if (hit) {
+                ny = list_normal(lists, o, w, h.t, slot, h.axis);
                 y = madd(o, h.t, w);
                 prim = h.prim;
                 const V3 v = y - g.pos;
@@ -935,6 +941,130 @@ __global__ void __launch_bounds__(NT, 4)
                 store_res(out, p_own, r);
             }
         }
+    }
+}
+
+// The candidate trace of the learned-cache form by tiles: k_cand's planes, bit
+// for bit, from the sorted rays and primitive lists of k_initial_tile.  A
+// thread keeps the directions of its RPT rays per round; through LDS go the
+// directions in sorted order, which their hits overwrite, and each ray's place.
+// Only the hits come back, so that a wave writes whole lines of the planes.
+// Bound by vector issue and the L1's return path, as k_initial_tile is, and by
+// the planes' 32 B a candidate: 1920x1080, M = 32, 256 primitives, the trace
+// alone 3.1 -> 2.0 ms (2.1 GB of planes: 1.1 TB/s).
+constexpr uint32_t cand_bytes(uint32_t rays, uint32_t pixels) { return rays * 14u + pixels * 12u + (kBins + 8u) * 4u; }
+
+template <int RPT>
+__global__ void __launch_bounds__(kTileBlock, 4)
+    k_cand_tile(gi_scene sc, gi_gbuffer gb, gi_params pp, CandWs ws, uint64_t seed, uint32_t frame, uint32_t lw,
+                uint32_t lh, gi_mlp mlp)
+{
+    if (gated_off(ws, mlp)) return;
+    constexpr uint32_t kRays = (uint32_t)kTileBlock * RPT;
+    const uint32_t t = threadIdx.x, TP = 1u << (lw + lh), M = pp.M, C = kRays >> (lw + lh);
+    TileLists lists(gi_lds, sc.n_prims);
+    float *const ray = reinterpret_cast<float *>(reinterpret_cast<char *>(gi_lds) + list_bytes(sc.n_prims));
+    uint32_t *const hist = reinterpret_cast<uint32_t *>(ray + 3u * kRays);
+    float *const orgs = reinterpret_cast<float *>(hist + kBins + 8u);
+    uint16_t *const owner = reinterpret_cast<uint16_t *>(orgs + 3u * TP);     // pixel (low) of the sorted rays
+
+    const uint32_t k = t & (TP - 1u);
+    uint32_t px, py;
+    tile_pixel_of(k, lw, lh, px, py);
+    const bool inside = px < gb.width && py < gb.height;
+    const uint32_t p = py * gb.width + px;
+    const size_t npx = (size_t)gb.width * gb.height;
+    V3 org = v3(0.0f, 0.0f, 0.0f), nrm = org;
+    bool on = false;
+    if (inside) {
+        const GB g = load_gb(gb, p);
+        on = active(g);
+        org = madd(g.pos, sc.eps, g.n);
+        nrm = g.n;
+    }
+    {
+        Box3 ob, nb;
+        block_boxes<kTileBlock>(org, nrm, on && fabsf(org.x) + fabsf(org.y) + fabsf(org.z) < kInf,
+                                reinterpret_cast<float4 *>(ray), ob, nb);
+        if (__syncthreads_or(on) != 0) build_lists<kTileBlock>(sc, lists, ob, nb, reinterpret_cast<uint32_t *>(ray));
+    }
+    if (t < TP) {
+        orgs[t] = org.x;
+        orgs[TP + t] = org.y;
+        orgs[2u * TP + t] = org.z;
+    }
+    const float miss = __uint_as_float(GI_MISS);
+#pragma unroll 1
+    for (uint32_t base = 0; base < M; base += C) {
+        for (uint32_t b = t; b < (uint32_t)kBins; b += kTileBlock) hist[b] = 0u;
+        __syncthreads();
+        V3 w[RPT];
+        uint32_t at[RPT];
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const uint32_t i = base + (((uint32_t)j * kTileBlock + t) >> (lw + lh));
+            at[j] = ~0u;
+            if (!on || i >= M) continue;
+            const uint4 rn = philox(seed, p, frame, kPassInitial, i);
+            w[j] = cosine_dir(nrm, u01(rn.x), u01(rn.y));
+            const uint32_t b = sort_bin_of(w[j]) >> 2;
+            at[j] = b | (atomicAdd(&hist[b], 1u) << 16);
+        }
+        __syncthreads();
+        if (t < 64u) bin_starts<kBins>(hist);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            if (at[j] == ~0u) continue;
+            const uint32_t b = at[j] & 0xFFFFu, a = hist[b] + (at[j] >> 16);
+            at[j] = a;
+            ray[a] = w[j].x;
+            ray[kRays + a] = w[j].y;
+            ray[2u * kRays + a] = w[j].z;
+            owner[a] = (uint16_t)k;
+        }
+        __syncthreads();
+        for (uint32_t a = t; a < hist[kBins]; a += kTileBlock) {
+            const V3 d = v3(ray[a], ray[kRays + a], ray[2u * kRays + a]);
+            const uint32_t q = owner[a];
+            Hit h;
+            uint32_t slot;
+            cast_lists(sc, lists, sort_bin_of(d) >> 2, v3(orgs[q], orgs[TP + q], orgs[2u * TP + q]), d, h, slot);
+            ray[a] = h.t;
+            // slot, or 2^16 + a wall's index, or ~0 for a miss
+            reinterpret_cast<uint32_t *>(ray)[kRays + a] = slot != ~0u ? slot : (h.prim == GI_MISS ? ~0u : 0x10000u + (h.prim - sc.n_prims));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const uint32_t i = base + (((uint32_t)j * kTileBlock + t) >> (lw + lh));
+            if (!inside || i >= M) continue;
+            float4 a = make_float4(0.0f, 0.0f, 0.0f, miss), b = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (at[j] != ~0u) {
+                const float ht = ray[at[j]];
+                uint32_t slot = reinterpret_cast<uint32_t *>(ray)[kRays + at[j]];
+                if (slot == ~0u) {
+                    a = make_float4(w[j].x, w[j].y, w[j].z, miss);
+                } else {
+                    const V3 y = madd(org, ht, w[j]);
+                    uint32_t prim;
+                    int axis = 0;
+                    if (slot >= 0x10000u) {
+                        prim = sc.n_prims + (slot - 0x10000u);
+                        axis = (int)((slot - 0x10000u) >> 1);
+                        slot = ~0u;
+                    } else {
+                        prim = lists.ids[slot];
+                    }
+                    const V3 ny = list_normal(lists, org, w[j], ht, slot, axis);
+                    a = make_float4(y.x, y.y, y.z, __uint_as_float(prim));
+                    b = make_float4(ny.x, ny.y, ny.z, 0.0f);
+                }
+            }
+            ws.pos[i * npx + p] = a;
+            ws.nrm[i * npx + p] = b;
+        }
+        __syncthreads();
     }
 }
 
@@ -1689,6 +1819,19 @@ bool tile_form(const gi_scene *sc, const gi_params *pp, uint32_t W, uint32_t H)
     return pp->M >= 24u || px >= 900000u || (px <= 96000u && 256u * pp->M >= 3u * sc->n_prims);
 }
 
+// Where the learned-cache form traces its candidates by tiles.  The walks it
+// replaces cost less than the probe form's pixels, so fewer frames gain: with
+// 256 primitives from M = 8 on (1920x1080: M = 32 5.69 -> 4.46 ms, M = 13
+// 2.33 -> 1.97, M = 8 1.47 -> 1.26, whole pass; 64x36, M = 32: 765 -> 234 us;
+// M = 4 0.81 -> 0.84); with 1024 the lists are longer and leave room for half
+// the rays per round, and only M = 32 gains (1920x1080 8.31 -> 7.91 ms; M = 13
+// 3.38 -> 3.72).
+bool cand_tiles(const gi_scene *sc, const gi_params &pp)
+{
+    if (sc->n_prims > kListMaxPrims || (sc->options & GI_OPT_NO_LDS) != 0u) return false;
+    return pp.M >= (sc->n_prims > 512u ? 24u : 8u);
+}
+
 bool glossy_scene(const gi_scene *sc) { return (sc->options & GI_OPT_GLOSSY) != 0u; }
 
 void launch_initial_tile(const gi_scene *sc, const gi_gbuffer &gb, const gi_probes &pr, const gi_params &pp,
@@ -1726,6 +1869,35 @@ void launch_initial_tile(const gi_scene *sc, const gi_gbuffer &gb, const gi_prob
     else if (px) { if (f16) GI_IT(false, kTexF16, true); else GI_IT(false, kTexF32, true); }
     else { if (f16) GI_IT(false, kTexF16, false); else GI_IT(false, kTexF32, false); }
 #undef GI_IT
+}
+
+void launch_cand(const gi_scene *sc, const gi_gbuffer &gb, const gi_params &pp, const CandWs &ws, uint64_t seed,
+                 uint32_t frame, const gi_mlp &mlp, hipStream_t st)
+{
+    const uint32_t W = gb.width, H = gb.height, lds = scene_lds(sc);
+    if (!cand_tiles(sc, pp)) {
+        GI_LAUNCH_LDS(k_cand, tile_grid(W, H), kBlock, lds, st, *sc, gb, pp, ws, seed, frame, mlp);
+        return;
+    }
+    // Some 4000 rays per tile, which two rounds trace; less, but not below
+    // 1000, where the image would not make 2048 tiles.  1920x1080: M = 32
+    // 16x8 4.46 ms (16x16 4.42, 32x16 4.64, 8x8 4.79), M = 13 16x16 1.97
+    // (16x8 2.13), M = 8 32x16 1.26 (16x16 1.29, 16x8 1.56); 320x180, M = 32:
+    // 8x8 299 us, 16x8 419, 16x16 679.
+    uint32_t lw = pp.M >= 12u ? 4u : 5u, lh = pp.M >= 24u ? 3u : 4u;
+    while (lw + lh > 6u && (pp.M << (lw + lh - 1u)) >= 1024u &&
+           (uint64_t)((W + (1u << lw) - 1u) >> lw) * ((H + (1u << lh) - 1u) >> lh) < 2048u) {
+        if (lw > lh) --lw;
+        else --lh;
+    }
+    const dim3 grid((W + (1u << lw) - 1u) >> lw, (H + (1u << lh) - 1u) >> lh);
+    const uint32_t list = list_bytes(sc->n_prims), TP = 1u << (lw + lh);
+    const uint32_t big = list + std::max(cand_bytes(4u * kTileBlock, TP), 4u * kListScratch);
+    if (big <= kTileLds)
+        k_cand_tile<4><<<grid, kTileBlock, big, st>>>(*sc, gb, pp, ws, seed, frame, lw, lh, mlp);
+    else
+        k_cand_tile<2><<<grid, kTileBlock, list + std::max(cand_bytes(2u * kTileBlock, TP), 4u * kListScratch), st>>>(
+            *sc, gb, pp, ws, seed, frame, lw, lh, mlp);
 }
 
 // the probe form of the initial pass
@@ -2024,8 +2196,7 @@ gi_status gi_resample_initial_mlp(const gi_scene *scene, const gi_gbuffer *gb, c
     if (mlp->mode != GI_MLP_NEVER) {
         const uint32_t gate = mlp->mode == GI_MLP_AUTO ? kRunIfCache : kRunAlways;
         CandWs ws{base, base + ncand, base + 2 * ncand, gate};
-        GI_LAUNCH_LDS(k_cand, tile_grid(W, H), kBlock, scene_lds(scene), S(stream), *scene, *gb, *params, ws, seed,
-                      frame, *mlp);
+        launch_cand(scene, *gb, *params, ws, seed, frame, *mlp, S(stream));
         if ((s = launched()) != GI_OK) return s;
         if ((s = mlp_infer_launch(*mlp, (uint32_t)ncand, ws.pos, ws.nrm, ws.q, true, S(stream))) != GI_OK) return s;
         launch_initial<true>(params->M_light > 0, false, probes->texel == GI_TEXEL_F16, 0u, tile_grid(W, H), S(stream), *scene, *gb, *probes,

@@ -282,9 +282,9 @@ __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Bo
 }
 
 // Closest hit of a ray of the tile (origin and cell b as the lists were built
-// for) as cast<false> finds it, and the facing normal there as hit_normal
-// forms it.
-__device__ __forceinline__ bool cast_lists(const gi_scene &sc, const TileLists &L, uint32_t b, V3 o, V3 d, Hit &h, V3 &n)
+// for) as cast<false> finds it; slot: the primitive's in the lists, or ~0
+__device__ __forceinline__ bool cast_lists(const gi_scene &sc, const TileLists &L, uint32_t b, V3 o, V3 d, Hit &h,
+                                           uint32_t &slot)
 {
     h.t = kInf;
     h.prim = GI_MISS;
@@ -297,7 +297,7 @@ __device__ __forceinline__ bool cast_lists(const gi_scene &sc, const TileLists &
         if (tw < h.t) { h.t = tw; h.prim = wall; h.axis = axis; }
     }
     const uint32_t *mask = L.mask + b * L.words;
-    uint32_t slot = ~0u;
+    slot = ~0u;
     const auto take = [&](float t, uint32_t s) {
         if (t <= h.t && t < kInf) {
             const uint32_t i = L.ids[s];
@@ -328,24 +328,27 @@ __device__ __forceinline__ bool cast_lists(const gi_scene &sc, const TileLists &
             take(isect_box(o, inv, v3(p.x, p.y, q.x), v3(q.y, r.x, r.y)), s);
         }
     }
-    if (h.prim == GI_MISS) return false;
-    const bool sphere = slot < 32u * L.sw;
-    if (sphere) {
+    return h.prim != GI_MISS;
+}
+
+// facing normal of a hit of cast_lists, as hit_normal forms it; a wall's
+// (slot ~0) has its axis in `axis`
+__device__ __forceinline__ V3 list_normal(const TileLists &L, V3 o, V3 d, float t, uint32_t slot, int axis)
+{
+    if (slot < 32u * L.sw) {
         const float2 p = L.geo[3u * slot], q = L.geo[3u * slot + 1u];
-        const V3 x = madd(o, h.t, d);
+        const V3 x = madd(o, t, d);
         const float ir = rcp(q.y);
-        n = ir * (x - v3(p.x, p.y, q.x));
-        if (dot(n, d) > 0.0f) n = -n;
-    } else {
-        int axis = h.axis;
-        if (slot != ~0u) {
-            const float2 p = L.geo[3u * slot], q = L.geo[3u * slot + 1u], r = L.geo[3u * slot + 2u];
-            axis = box_axis(o, inv, v3(p.x, p.y, q.x), v3(q.y, r.x, r.y));
-        }
-        const float s = comp(d, axis) > 0.0f ? -1.0f : 1.0f;
-        n = v3(axis == 0 ? s : 0.0f, axis == 1 ? s : 0.0f, axis == 2 ? s : 0.0f);
+        const V3 n = ir * (x - v3(p.x, p.y, q.x));
+        return dot(n, d) > 0.0f ? -n : n;
     }
-    return true;
+    if (slot != ~0u) {
+        const V3 inv = v3(rcp(d.x), rcp(d.y), rcp(d.z));
+        const float2 p = L.geo[3u * slot], q = L.geo[3u * slot + 1u], r = L.geo[3u * slot + 2u];
+        axis = box_axis(o, inv, v3(p.x, p.y, q.x), v3(q.y, r.x, r.y));
+    }
+    const float s = comp(d, axis) > 0.0f ? -1.0f : 1.0f;
+    return v3(axis == 0 ? s : 0.0f, axis == 1 ? s : 0.0f, axis == 2 ? s : 0.0f);
 }
 
 }  // namespace gi
