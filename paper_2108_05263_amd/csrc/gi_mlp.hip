@@ -130,9 +130,10 @@ struct InferSrc {
     float scale;
 };
 
-__device__ __forceinline__ InferSrc infer_src(const gi_mlp &m)
+// step: the optimiser step whose parameters these are, 0: the state's
+__device__ __forceinline__ InferSrc infer_src(const gi_mlp &m, uint32_t step)
 {
-    const uint32_t t = m.state[GI_MLP_STATE_STEPS];
+    const uint32_t t = step ? step : m.state[GI_MLP_STATE_STEPS];
     if (m.ema && t > 0u) return InferSrc{m.ema, 1.0f / (1.0f - powf(m.ema_decay, (float)t))};
     return InferSrc{m.params, 1.0f};
 }
@@ -145,11 +146,57 @@ __device__ __forceinline__ void write_bias(const gi_mlp &m, const InferSrc &src,
     reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(m.weights) + kBiasOff)[i] = b;
 }
 
-// BF16 fragments: element i = (f * 64 + lane) * 8 + v
-__global__ void __launch_bounds__(256) k_mlp_prepare_bf16(gi_mlp m)
+// sum of a value over a 1024-thread workgroup: wave sums by shuffles, then
+// the 16 wave sums in order (integer-valued here, so exact)
+__device__ __forceinline__ uint32_t block_sum_1024(uint32_t v, uint32_t *red)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const InferSrc src = infer_src(m);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    uint32_t r = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) r += red[w];
+    return r;
+}
+
+// usability after step t, by one workgroup of 1024 threads
+constexpr int kPrepBlock = 1024;
+__device__ __forceinline__ void update_state(const gi_mlp &m, uint32_t t)
+{
+    __shared__ uint32_t red[16];
+    // all of a thread's loads in flight at once
+    uint32_t bad = 0;
+    constexpr int kPer = (kParams + kPrepBlock - 1) / kPrepBlock;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int p = threadIdx.x + kPrepBlock * k;
+        if (p < kParams) bad += __builtin_isfinite(m.params[p]) ? 0u : 1u;
+    }
+    const uint32_t nonfinite = block_sum_1024(bad, red);
+    if (threadIdx.x == 0) {
+        const float be = __uint_as_float(m.state[GI_MLP_STATE_BATCH_ERR]);
+        const float old = __uint_as_float(m.state[GI_MLP_STATE_EMA_ERR]);
+        const float ema = t <= 1u ? be : 0.9f * old + 0.1f * be;
+        const bool ok = t >= m.warmup_steps && m.state[GI_MLP_STATE_NONFINITE] == 0u && ema <= m.max_rel_err &&
+                        nonfinite == 0u;
+        m.state[GI_MLP_STATE_STEPS] = t;
+        m.state[GI_MLP_STATE_EMA_ERR] = __float_as_uint(ema);
+        m.state[GI_MLP_STATE_USABLE] = ok ? 1u : 0u;
+    }
+}
+
+// BF16 fragments: element i = (f * 64 + lane) * 8 + v; after step > 0 one more
+// workgroup updates the state, which the others do not read then
+constexpr uint32_t kPrepBf16 = (kFrags * 64 * 8 + kPrepBlock - 1) / kPrepBlock;
+__global__ void __launch_bounds__(kPrepBlock) k_mlp_prepare_bf16(gi_mlp m, uint32_t step)
+{
+    if (blockIdx.x == kPrepBf16) {
+        update_state(m, step);
+        return;
+    }
+    const int i = blockIdx.x * kPrepBlock + threadIdx.x;
+    const InferSrc src = infer_src(m, step);
     if (i < kBiasSlots) write_bias(m, src, i);
     if (i >= kFrags * 64 * 8) return;
     const int f = i >> 9, l = (i >> 3) & 63, v = i & 7;
@@ -198,20 +245,26 @@ __device__ __forceinline__ int exp2_of(float pow2)
     return e - 1;
 }
 
-__global__ void __launch_bounds__(256) k_mlp_wscale(gi_mlp m)
+// one workgroup per layer, and after step > 0 one more that updates the state
+__global__ void __launch_bounds__(kPrepBlock) k_mlp_wscale(gi_mlp m, uint32_t step)
 {
-    __shared__ float red[256];
-    const int L = blockIdx.x, t = threadIdx.x, cnt = kIn[L] * kOut[L];
-    const InferSrc src = infer_src(m);
-    float a = 0.0f;
-    for (int i = t; i < cnt; i += 256) a = fmaxf(a, fabsf(src.p[kOffW[L] + i] * src.scale));
-    red[t] = a;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (t < o) red[t] = fmaxf(red[t], red[t + o]);
-        __syncthreads();
+    if (blockIdx.x == (uint32_t)kLayers) {
+        update_state(m, step);
+        return;
     }
-    if (t == 0) m.scales[L] = fp8_scale(red[0]);
+    __shared__ float wmax[kPrepBlock / 64];
+    const int L = blockIdx.x, t = threadIdx.x, cnt = kIn[L] * kOut[L];
+    const InferSrc src = infer_src(m, step);
+    float a = 0.0f;
+    for (int i = t; i < cnt; i += kPrepBlock) a = fmaxf(a, fabsf(src.p[kOffW[L] + i] * src.scale));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) a = fmaxf(a, __shfl_xor(a, o, 64));
+    if ((t & 63) == 0) wmax[t >> 6] = a;
+    __syncthreads();
+    if (t == 0) {
+        for (int w = 1; w < kPrepBlock / 64; ++w) a = fmaxf(a, wmax[w]);
+        m.scales[L] = fp8_scale(a);
+    }
 }
 
 __device__ __forceinline__ uint32_t fp8_byte(float x)
@@ -239,10 +292,10 @@ __host__ __device__ constexpr int k64_unit(int h, int b)
     return 32 * (b >> 4) + 8 * ((b >> 2) & 3) + 4 * h + (b & 3);
 }
 
-__global__ void __launch_bounds__(256) k_mlp_prepare_fp8(gi_mlp m)
+__global__ void __launch_bounds__(256) k_mlp_prepare_fp8(gi_mlp m, uint32_t step)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    const InferSrc src = infer_src(m);
+    const InferSrc src = infer_src(m, step);
     if (i < kBiasSlots) write_bias(m, src, i);
     if (i >= kFp8Frags * 64 * 32) return;
     const int f = i >> 11, l = (i >> 5) & 63, b = i & 31, h = l >> 5;
@@ -620,52 +673,27 @@ k_mlp_infer_fp8(gi_mlp m, uint32_t n, const float4 *pos, const float4 *nrm, floa
 // --------------------------------------------------------------------------
 // training
 // --------------------------------------------------------------------------
-// number of valid samples (target.w != 0) -> hdr[0]
-// sum of a value over a 1024-thread workgroup: wave sums by shuffles, then
-// the 16 wave sums in order (integer-valued here, so exact)
-__device__ __forceinline__ uint32_t block_sum_1024(uint32_t v, uint32_t *red)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    uint32_t r = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) r += red[w];
-    return r;
-}
-
-__global__ void __launch_bounds__(1024) k_mlp_count(uint32_t n, const float4 *tgt, uint32_t *hdr)
-{
-    __shared__ uint32_t red[16];
-    // 16 independent loads in flight per thread and round
-    uint32_t c = 0;
-    for (uint32_t i = threadIdx.x; i < n; i += 16384) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const uint32_t j = i + 1024u * k;
-            if (j < n) c += tgt[j].w != 0.0f ? 1u : 0u;
-        }
-    }
-    const uint32_t r = block_sum_1024(c, red);
-    if (threadIdx.x == 0) hdr[0] = r;
-}
-
 // --------------------------------------------------------------------------
 // training on the matrix cores
 // --------------------------------------------------------------------------
-// One workgroup of two waves takes kMS = 64 samples, each wave a tile of 32
-// samples on the N side of the 32x32x16 BF16 product, as in inference:
-// forward products W x (weight fragments of the master parameters as the A
-// operand), the activations handed from layer to layer in registers, and
-// each layer's input also written to LDS unit-major ([unit][sample]); the
-// backward products dA = W^T g take the transposed fragments, g handed down
-// in registers the same way (the ReLU masks kept as bits from the forward
-// pass); the weight gradients dW = g^T a sum over the 64 samples with the
-// samples on the K side, both operands read from LDS.  Every operand is
-// rounded to BF16 and products accumulate in FP32, as in the VALU form.
+// One workgroup of four waves takes kMS = 64 samples: two tiles of 32 samples
+// on the N side of the 32x32x16 BF16 product, as in inference, times the two
+// row tiles of every product.  Forward products W x take the weight fragments
+// of the master parameters as the A operand; a wave keeps its row tile's
+// activations in registers as operands of the next layer, exchanges them with
+// the wave of the other row tile through LDS, and writes each layer's input
+// to LDS unit-major ([unit][sample]); the backward products dA = W^T g take
+// the transposed fragments, g handed down the same way (the ReLU masks kept as
+// bits from the forward pass); the weight gradients dW = g^T a sum over the 64
+// samples with the samples on the K side, both operands read from LDS, a tile
+// per wave.  Every operand is rounded to BF16 and products accumulate in FP32.
+// Bound by the latency of one wave's chain, since 16,384 samples give each CU
+// one workgroup: with two waves, each taking both row tiles, 34.3 us, with
+// four, one barrier per layer and the prologue's loads in flight together
+// 20.7; the step's eight launches, 58.4 us, are now four, 31.9 us (65,536
+// samples: 159 -> 94 us).
 constexpr int kMS = 64;                 // samples per workgroup
-constexpr int kMBlock = 128;            // two waves
+constexpr int kMBlock = 256;            // four waves
 constexpr int kFwdFrags = kFrags;       // 38 forward fragments (inference layout, master parameters)
 constexpr int kBwdFrag0[kLayers] = {0, 0, 8, 16, 24};   // backward fragments of layers 1..4 (W^T)
 constexpr int kBwdFrags = 26;
@@ -687,10 +715,33 @@ __device__ __forceinline__ float bwd_weight(const float *P, int f, int l, int v)
     return P[kOffW[L] + u * kIn[L] + k];
 }
 
-// forward and backward BF16 fragments of the master parameters, one element per thread
-__global__ void __launch_bounds__(256) k_mlp_train_frags(gi_mlp m, __bf16 *frags)
+// Workgroups 0..kCountWgs-1 count the valid samples (target.w != 0) of every
+// kCountWgs-th run of 256 into hdr[0..kCountWgs-1]; the others make the forward
+// and backward BF16 fragments of the master parameters, one element per thread.
+// (One workgroup counting alone took 6.3 us for 16,384 samples, and the
+// fragments 1.8 us after it; together 2.6 us.)
+constexpr uint32_t kCountWgs = 32;
+__global__ void __launch_bounds__(256) k_mlp_train_prep(gi_mlp m, uint32_t n, const float4 *tgt, uint32_t *hdr,
+                                                        __bf16 *frags)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x < kCountWgs) {
+        __shared__ uint32_t red[4];
+        uint32_t c = 0;
+        for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += 8u * 256u * kCountWgs) {
+#pragma unroll
+            for (uint32_t k = 0; k < 8u; ++k) {
+                const uint32_t j = i + 256u * kCountWgs * k;
+                if (j < n) c += tgt[j].w != 0.0f ? 1u : 0u;
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = c;
+        __syncthreads();
+        if (threadIdx.x == 0) hdr[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+        return;
+    }
+    const int i = (blockIdx.x - kCountWgs) * 256 + threadIdx.x;
     if (i >= (kFwdFrags + kBwdFrags) * 64 * 8) return;
     const int f = i >> 9, l = (i >> 3) & 63, v = i & 7;
     float w = 0.0f;
@@ -703,6 +754,16 @@ __global__ void __launch_bounds__(256) k_mlp_train_frags(gi_mlp m, __bf16 *frags
         w = bwd_weight(m.params, f - kFwdFrags, l, v);
     }
     frags[i] = (__bf16)w;
+}
+
+// the number of valid samples, on every lane of the wave
+__device__ __forceinline__ uint32_t valid_count(const uint32_t *hdr)
+{
+    static_assert(kCountWgs == 32 && kCountWgs <= (uint32_t)kHdr, "one count per lane of a half-wave");
+    uint32_t c = hdr[threadIdx.x & 31];
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+    return c;
 }
 
 // sum over the 32 lanes of each half-wave (fixed butterfly order)
@@ -753,30 +814,48 @@ __global__ void __launch_bounds__(kMBlock) k_mlp_fwdbwd_mfma(gi_mlp m, uint32_t 
 {
     __shared__ __attribute__((aligned(16))) __bf16 sX[80 * kMS];       // layer 0 input [feature][sample]
     __shared__ __attribute__((aligned(16))) __bf16 sA[4 * 64 * kMS];   // layer 1..4 inputs [unit][sample]
-    __shared__ __attribute__((aligned(16))) __bf16 sG[64 * kMS];       // BF16 gradient [unit][sample]
-    __shared__ float sDb[2][64];                                       // bias gradient per wave
-    __shared__ float sSt[2][kStats];
+    __shared__ __attribute__((aligned(16))) __bf16 sG[2][64 * kMS];    // BF16 gradient [unit][sample]
+    __shared__ bf16x8 sOp[2][2][4][64];                                // operands on their way to the other row tile's wave
+    __shared__ float sDb[2][2][64];                                    // bias gradient per sample tile
+    __shared__ float sSt[4][kStats];
     // all 64 forward and backward fragments staged in LDS (64 KB): each
     // layer's operands are then an LDS read away instead of an L2 round trip
     __shared__ bf16x8 sF[(kFwdFrags + kBwdFrags) * 64];
-    for (int i = threadIdx.x; i < (kFwdFrags + kBwdFrags) * 64; i += kMBlock) sF[i] = frags[i];
     // the biases too (layer L's at 64 L, the output layer's at 256)
-    __shared__ float sBias[kBiasSlots];
-    for (int i = threadIdx.x; i < kBiasSlots; i += kMBlock) {
-        const int L = i < 256 ? i >> 6 : 4, u = i < 256 ? i & 63 : i - 256;
-        sBias[i] = u < kOut[L] ? m.params[kOffB[L] + u] : 0.0f;
-    }
+    __shared__ __attribute__((aligned(16))) float sBias[kBiasSlots];
 
-    const int wv = threadIdx.x >> 6, l = threadIdx.x & 63, s = l & 31, h = l >> 5;
-    const int sl = 32 * wv + s;                                        // sample within the workgroup
+    // wave: sample tile sw, row tile rt of every product
+    const int wv = threadIdx.x >> 6, l = threadIdx.x & 63, s = l & 31, h = l >> 5, sw = wv & 1, rt = wv >> 1;
+    const int sl = 32 * sw + s;                                        // sample within the workgroup
     const uint32_t idx = blockIdx.x * kMS + sl;
     float *pw = part + (size_t)blockIdx.x * kPartStride;
     const bf16x8 *bfr = sF + kFwdFrags * 64;
 
-    // inputs and encoding: lanes 0-31 the position's 39 features, 32-63 the normal's
+    // every load of the prologue is issued before the first is used
     const float4 tg = idx < n ? tgt[idx] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const bool valid = idx < n && tg.w != 0.0f;
-    const float4 in = valid ? (h ? nrm[idx] : pos[idx]) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float4 in = make_float4(0.0f, 0.0f, 0.0f, 0.0f), q = in;
+    if (idx < n) {
+        in = h ? nrm[idx] : pos[idx];
+        if (qp) q = qp[idx];
+    }
+    if (!valid) in = q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const uint32_t count = valid_count(hdr);
+    constexpr int kLoads = (kFwdFrags + kBwdFrags) * 64 / kMBlock;
+    static_assert(kLoads * kMBlock == (kFwdFrags + kBwdFrags) * 64, "whole rounds");
+    {
+        bf16x8 r[kLoads];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) r[i] = frags[i * kMBlock + threadIdx.x];
+        for (int i = threadIdx.x; i < kBiasSlots; i += kMBlock) {
+            const int L = i < 256 ? i >> 6 : 4, u = i < 256 ? i & 63 : i - 256;
+            sBias[i] = u < kOut[L] ? m.params[kOffB[L] + u] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) sF[i * kMBlock + threadIdx.x] = r[i];
+    }
+
+    // inputs and encoding: lanes 0-31 the position's 39 features, 32-63 the normal's
     float feat[40];
     float amax[kLayers] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -787,90 +866,79 @@ __global__ void __launch_bounds__(kMBlock) k_mlp_fwdbwd_mfma(gi_mlp m, uint32_t 
     for (int j = 0; j < 39; ++j) {
         if (!valid) feat[j] = 0.0f;
         amax[0] = fmaxf(amax[0], fabsf(feat[j]));
-        sX[(39 * h + j) * kMS + sl] = (__bf16)feat[j];
+        if ((j >= 20) == (rt == 1)) sX[(39 * h + j) * kMS + sl] = (__bf16)feat[j];
     }
-    if (h) {
+    if (h && rt) {
         sX[78 * kMS + sl] = (__bf16)0.0f;
         sX[79 * kMS + sl] = (__bf16)0.0f;
     }
 
-    __syncthreads();   // sF
+    __syncthreads();   // sF, sBias
+
+    // the operands of the row tile in v (c = 2 rt, 2 rt + 1) go to the other
+    // row tile's wave of the same samples, and the other way
+    const auto send = [&](int buf, const bf16x8 own[2]) {
+        sOp[buf][sw][2 * rt][l] = own[0];
+        sOp[buf][sw][2 * rt + 1][l] = own[1];
+    };
+    const auto receive = [&](int buf, const bf16x8 own[2], bf16x8 op[4]) {
+        const bf16x8 o0 = sOp[buf][sw][2 - 2 * rt][l], o1 = sOp[buf][sw][3 - 2 * rt][l];
+        op[0] = rt ? o0 : own[0];
+        op[1] = rt ? o1 : own[1];
+        op[2] = rt ? own[0] : o0;
+        op[3] = rt ? own[1] : o1;
+    };
 
     // forward
     uint32_t mask[kLayers - 1];
-    f32x16 acc0, acc1;
-    {
-        acc0 = f32x16{};
-        acc1 = f32x16{};
+    f32x16 acc = bias_tile(sBias + 32 * rt, h);
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+    for (int c = 0; c < 5; ++c) {
+        f32x8 x;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                acc0[4 * a + b] = sBias[8 * a + 4 * h + b];
-                acc1[4 * a + b] = sBias[32 + 8 * a + 4 * h + b];
-            }
-#pragma unroll
-        for (int c = 0; c < 5; ++c) {
-            f32x8 x;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) x[v] = feat[8 * c + v];
-            const bf16x8 b = to_bf16(x);
-            acc0 = mfma(sF[c * 64 + l], b, acc0);
-            acc1 = mfma(sF[(5 + c) * 64 + l], b, acc1);
-        }
+        for (int v = 0; v < 8; ++v) x[v] = feat[8 * c + v];
+        acc = mfma(sF[(5 * rt + c) * 64 + l], to_bf16(x), acc);
     }
 #pragma unroll
     for (int L = 1; L < kLayers; ++L) {
         // layer L-1's ReLU output: kept as the ReLU mask and written to LDS as layer L's input
+        const bf16x8 own[2] = {relu_operand(acc, 0), relu_operand(acc, 1)};
+        send(L & 1, own);
         uint32_t mk = 0u;
         float mx = 0.0f;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float z = t ? acc1[i] : acc0[i];
-                const float a = fmaxf(z, 0.0f);
-                mk |= (z > 0.0f ? 1u : 0u) << (16 * t + i);
-                mx = fmaxf(mx, a);
-                const int k = 32 * t + 8 * (i >> 2) + 4 * h + (i & 3);
-                sA[((L - 1) * 64 + k) * kMS + sl] = (__bf16)a;
-            }
+        for (int i = 0; i < 16; ++i) {
+            const float z = acc[i], a = fmaxf(z, 0.0f);
+            mk |= (z > 0.0f ? 1u : 0u) << i;
+            mx = fmaxf(mx, a);
+            const int k = 32 * rt + 8 * (i >> 2) + 4 * h + (i & 3);
+            sA[((L - 1) * 64 + k) * kMS + sl] = (__bf16)a;
+        }
         mask[L - 1] = mk;
         if (valid) amax[L] = mx;
-        bf16x8 bop[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) bop[c] = relu_operand(c >> 1 ? acc1 : acc0, c & 1);
-        const int f0 = kFrag0[L];
+        __syncthreads();
+        bf16x8 op[4];
+        receive(L & 1, own, op);
+        const int f0 = kFrag0[L] + (L < kLayers - 1 ? 4 * rt : 0);
         if (L < kLayers - 1) {
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    acc0[4 * a + b] = sBias[64 * L + 8 * a + 4 * h + b];
-                    acc1[4 * a + b] = sBias[64 * L + 32 + 8 * a + 4 * h + b];
-                }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                acc0 = mfma(sF[(f0 + c) * 64 + l], bop[c], acc0);
-                acc1 = mfma(sF[(f0 + 4 + c) * 64 + l], bop[c], acc1);
-            }
+            acc = bias_tile(sBias + 64 * L + 32 * rt, h);
         } else {
-            acc0 = f32x16{};
+            // the output layer has one row tile: both waves form it
+            acc = f32x16{};
 #pragma unroll
-            for (int b = 0; b < 3; ++b) acc0[b] = h ? 0.0f : sBias[256 + b];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc0 = mfma(sF[(f0 + c) * 64 + l], bop[c], acc0);
+            for (int b = 0; b < 3; ++b) acc[b] = h ? 0.0f : sBias[256 + b];
         }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc = mfma(sF[(f0 + c) * 64 + l], op[c], acc);
     }
     // loss gradient (lower half-wave: outputs 0..2 in accumulators 0..2)
-    const float ntot = (float)max(hdr[0], 1u) * 3.0f;
+    const float ntot = (float)max(count, 1u) * 3.0f;
     float loss = 0.0f, enum_ = 0.0f, eden = 0.0f, nonfinite = 0.0f;
     float g[3] = {0.0f, 0.0f, 0.0f};
     if (h == 0) {
-        const float4 q = (valid && qp) ? qp[idx] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const float z = acc0[c];
+            const float z = acc[c];
             if (valid) {
                 const float den = z * z + 0.01f, d = z - comp(tg, c);
                 g[c] = 2.0f * d / den / ntot;
@@ -886,7 +954,7 @@ __global__ void __launch_bounds__(kMBlock) k_mlp_fwdbwd_mfma(gi_mlp m, uint32_t 
             }
         }
     }
-    // statistics of the workgroup: per half-wave, then the two waves in order
+    // statistics of the wave: per half-wave, then the two halves
     {
         float st[4 + kLayers] = {loss, enum_, eden, nonfinite};
 #pragma unroll
@@ -902,106 +970,96 @@ __global__ void __launch_bounds__(kMBlock) k_mlp_fwdbwd_mfma(gi_mlp m, uint32_t 
     }
 
     // backward: layer 4 first (3 output units)
-    f32x16 g0, g1;     // this lane's gradient of the current layer's pre-activation
+    f32x16 gr = f32x16{};  // this lane's gradient of its row tile of the current layer's pre-activation
     // unrolled: every layer's sizes and offsets are constants
 #pragma unroll
     for (int L = kLayers - 1; L >= 0; --L) {
-        const int out = kOut[L], in = kIn[L];
+        const int out = kOut[L], in_ = kIn[L], buf = L & 1;
         // bias gradient (unrounded FP32 g) and the BF16 gradient in LDS [unit][sample]
+        bf16x8 own[2], op[4];
         if (L == kLayers - 1) {
+            if (rt == 0) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const float sum = half_sum_dpp(g[c]);
-                if (l == 31) sDb[wv][c] = sum;
-            }
-            if (h == 0) {
+                for (int c = 0; c < 3; ++c) {
+                    const float sum = half_sum_dpp(g[c]);
+                    if (l == 31) sDb[buf][sw][c] = sum;
+                }
+                if (h == 0) {
 #pragma unroll
-                for (int c = 0; c < 3; ++c) sG[c * kMS + sl] = (__bf16)g[c];
+                    for (int c = 0; c < 3; ++c) sG[buf][c * kMS + sl] = (__bf16)g[c];
+                }
             }
         } else {
+            if (L > 0) {
+                own[0] = bf16_operand(gr, 0);
+                own[1] = bf16_operand(gr, 1);
+                send(buf, own);
+            }
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float v = t ? g1[i] : g0[i];
-                    const int u = 32 * t + 8 * (i >> 2) + 4 * h + (i & 3);
-                    const float sum = half_sum_dpp(v);
-                    if (s == 31) sDb[wv][u] = sum;
-                    sG[u * kMS + sl] = (__bf16)v;
-                }
+            for (int i = 0; i < 16; ++i) {
+                const int u = 32 * rt + 8 * (i >> 2) + 4 * h + (i & 3);
+                const float sum = half_sum_dpp(gr[i]);
+                if (s == 31) sDb[buf][sw][u] = sum;
+                sG[buf][u * kMS + sl] = (__bf16)gr[i];
+            }
         }
+        // one barrier per layer: the next layer writes the other buffers
         __syncthreads();
-        if (threadIdx.x < out) pw[kOffB[L] + threadIdx.x] = sDb[0][threadIdx.x] + sDb[1][threadIdx.x];
+        if ((int)threadIdx.x < out) pw[kOffB[L] + threadIdx.x] = sDb[buf][0][threadIdx.x] + sDb[buf][1][threadIdx.x];
+        // dA = W^T g: the BF16 gradient from registers as the B operand
+        if (L > 0) {
+            f32x16 d = f32x16{};
+            if (L == kLayers - 1) {
+                f32x8 x = f32x8{};
+                if (h == 0) {
+                    x[0] = g[0];
+                    x[1] = g[1];
+                    x[2] = g[2];
+                }
+                d = mfma(bfr[(kBwdFrag0[L] + rt) * 64 + l], to_bf16(x), d);
+            } else {
+                receive(buf, own, op);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) d = mfma(bfr[(kBwdFrag0[L] + 4 * rt + c) * 64 + l], op[c], d);
+            }
+            // ReLU mask of layer L-1's output
+            const uint32_t mk = mask[L - 1];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) gr[i] = (mk >> i) & 1u ? d[i] : 0.0f;
+        }
         // dW = g^T a over the workgroup's 64 samples: output tiles (unit tile i, input tile j)
         const __bf16 *Ain = L == 0 ? sX : sA + (L - 1) * 64 * kMS;
-        const int ti = (out + 31) / 32, tj = (in + 31) / 32;
-        for (int tile = wv; tile < ti * tj; tile += 2) {
+        const int ti = (out + 31) / 32, tj = (in_ + 31) / 32;
+        for (int tile = wv; tile < ti * tj; tile += 4) {
             const int i0 = 32 * (tile / tj), j0 = 32 * (tile % tj);
             const int ur = i0 + (l & 31), kr = j0 + (l & 31);
             f32x16 d = f32x16{};
 #pragma unroll
             for (int c = 0; c < kMS / 16; ++c) {
                 const int s0 = 16 * c + 8 * h;
-                const bf16x8 a = ur < out ? *reinterpret_cast<const bf16x8 *>(sG + ur * kMS + s0) : bf16x8{};
-                const bf16x8 b = kr < (L == 0 ? 80 : in) ? *reinterpret_cast<const bf16x8 *>(Ain + kr * kMS + s0)
-                                                         : bf16x8{};
+                const bf16x8 a = ur < out ? *reinterpret_cast<const bf16x8 *>(sG[buf] + ur * kMS + s0) : bf16x8{};
+                const bf16x8 b = kr < (L == 0 ? 80 : in_) ? *reinterpret_cast<const bf16x8 *>(Ain + kr * kMS + s0)
+                                                          : bf16x8{};
                 d = mfma(a, b, d);
             }
             // accumulator 4a + b: row (unit) i0 + 8a + 4h + b, column (input) kr
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int u = i0 + 8 * (i >> 2) + 4 * h + (i & 3);
-                if (u < out && kr < in) pw[kOffW[L] + u * in + kr] = d[i];
+                if (u < out && kr < in_) pw[kOffW[L] + u * in_ + kr] = d[i];
             }
         }
-        if (L == 0) break;
-        // dA = W^T g: the BF16 gradient from registers as the B operand
-        bf16x8 bop[4];
-        int nc;
-        if (L == kLayers - 1) {
-            f32x8 x = f32x8{};
-            if (h == 0) {
-                x[0] = g[0];
-                x[1] = g[1];
-                x[2] = g[2];
-            }
-            bop[0] = to_bf16(x);
-            nc = 1;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) bop[c] = bf16_operand(c >> 1 ? g1 : g0, c & 1);
-            nc = 4;
-        }
-        f32x16 d0 = f32x16{}, d1 = f32x16{};
-        const int fb = kBwdFrag0[L];
-        for (int c = 0; c < nc; ++c) {
-            const int f0 = L == kLayers - 1 ? fb : fb + c, f1 = L == kLayers - 1 ? fb + 1 : fb + 4 + c;
-            d0 = mfma(bfr[f0 * 64 + l], bop[c], d0);
-            d1 = mfma(bfr[f1 * 64 + l], bop[c], d1);
-        }
-        // ReLU mask of layer L-1's output
-        const uint32_t mk = mask[L - 1];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            g0[i] = (mk >> i) & 1u ? d0[i] : 0.0f;
-            g1[i] = (mk >> (16 + i)) & 1u ? d1[i] : 0.0f;
-        }
-        __syncthreads();     // sG and sDb are rewritten by the next layer
     }
-    __syncthreads();
     if (threadIdx.x < kStats) {
-        // slots 0-3 sums (loss, error numerator and denominator, non-finite outputs), 4-8 the
-        // activation amax of every layer input, the rest unused (zero)
+        // slots 0-3 sums (loss, error numerator and denominator, non-finite outputs: both row
+        // tiles' waves hold them), 4-8 the activation amax of every layer input, the rest unused (zero)
         const int j = threadIdx.x;
-        const float v = j < 4 ? sSt[0][j] + sSt[1][j] : (j < 4 + kLayers ? fmaxf(sSt[0][j], sSt[1][j]) : 0.0f);
+        float v = 0.0f;
+        if (j < 4) v = sSt[0][j] + sSt[1][j];
+        else if (j < 4 + kLayers) v = fmaxf(fmaxf(sSt[0][j], sSt[1][j]), fmaxf(sSt[2][j], sSt[3][j]));
         pw[kParams + j] = v;
     }
 }
-
-// First level of the ordered reduction: rows g*kGroup .. g*kGroup+kGroup-1
-// of the partials are summed in order (max for the amax slots) into row
-// g*kGroup; each thread owns one column, so the in-place write is private.
-constexpr uint32_t kGroup = 16;
 
 __device__ __forceinline__ bool stat_is_max(int p)
 {
@@ -1009,55 +1067,70 @@ __device__ __forceinline__ bool stat_is_max(int p)
     return j >= kStAmax0 && j < kStAmax0 + kLayers;
 }
 
-__global__ void __launch_bounds__(256) k_mlp_reduce1(uint32_t nwg, float *part)
+__device__ __forceinline__ void adam(const gi_mlp &m, int p, float g, float lr, float c1, float c2)
 {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= kParams + kStats) return;
-    const uint32_t w0 = blockIdx.y * kGroup, w1 = min(w0 + kGroup, nwg);
-    const bool is_max = stat_is_max(p);
-    // the group's loads are all issued before the first add; the order of
-    // the adds is the partials' order
-    float x[kGroup];
-#pragma unroll
-    for (uint32_t k = 0; k < kGroup; ++k) x[k] = w0 + k < w1 ? part[(size_t)(w0 + k) * kPartStride + p] : 0.0f;
-    float acc = 0.0f;
-#pragma unroll
-    for (uint32_t k = 0; k < kGroup; ++k) acc = is_max ? fmaxf(acc, x[k]) : acc + x[k];
-    part[(size_t)w0 * kPartStride + p] = acc;
+    const float mm = 0.9f * m.adam_m[p] + 0.1f * g;
+    const float vv = 0.99f * m.adam_v[p] + 0.01f * g * g;
+    m.adam_m[p] = mm;
+    m.adam_v[p] = vv;
+    const float np = m.params[p] - lr * (mm * c1) / (sqrtf(vv * c2) + 1e-8f);
+    m.params[p] = np;
+    if (m.ema) m.ema[p] = m.ema_decay * m.ema[p] + (1.0f - m.ema_decay) * np;
 }
 
-// second level: the group sums in group order; statistics into state / scales
-__global__ void __launch_bounds__(256) k_mlp_reduce(gi_mlp m, uint32_t nwg, const float *part, float *grad,
-                                                    const uint32_t *hdr)
+// Ordered reduction of the partials: kGroup consecutive rows are summed in
+// order (max for the amax slots), then the groups' sums in group order.  A
+// workgroup takes 32 columns of kGroup groups at a time, its last one the
+// statistics, which go into state / scales; every load of a thread is issued
+// before its first add.  Bound by reading the partials (18 MB for 16,384
+// samples, from the caches that they were just written to): 6.2 us with the
+// optimiser, where two passes and the optimiser behind them took 10.2.
+// ADAM: the gradient goes straight into the optimiser step as well
+constexpr uint32_t kGroup = 16, kRedCols = 32, kRedWgs = (kParams + kRedCols - 1) / kRedCols + 1;
+
+template <bool ADAM>
+__global__ void __launch_bounds__(kRedCols * kGroup) k_mlp_reduce(gi_mlp m, uint32_t nwg, const float *part, float *grad,
+                                                                  const uint32_t *hdr, float lr, float c1, float c2)
 {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= kParams + kStats) return;
-    const int j = p - kParams;
-    const bool is_max = stat_is_max(p);
-    // group sums in group order, 16 loads in flight per round
+    static_assert(kStats <= (int)kRedCols, "one workgroup takes the statistics");
+    __shared__ float sum[kGroup][kRedCols];
+    const uint32_t col = threadIdx.x % kRedCols, grp = threadIdx.x / kRedCols;
+    const bool stats = blockIdx.x == kRedWgs - 1u;
+    const int p = stats ? kParams + (int)col : (int)(blockIdx.x * kRedCols + col);
+    const bool on = stats ? col < (uint32_t)kStats : p < kParams, is_max = stat_is_max(p);
     float acc = 0.0f;
-    for (uint32_t w = 0; w < nwg; w += 16 * kGroup) {
-        float x[16];
+    for (uint32_t w = 0; w < nwg; w += kGroup * kGroup) {
+        const uint32_t w0 = w + grp * kGroup;
+        float x[kGroup];
 #pragma unroll
-        for (uint32_t k = 0; k < 16; ++k) {
-            const uint32_t wk = w + k * kGroup;
-            x[k] = wk < nwg ? part[(size_t)wk * kPartStride + p] : 0.0f;
-        }
+        for (uint32_t k = 0; k < kGroup; ++k) x[k] = on && w0 + k < nwg ? part[(size_t)(w0 + k) * kPartStride + p] : 0.0f;
+        float a = 0.0f;
 #pragma unroll
-        for (uint32_t k = 0; k < 16; ++k) acc = is_max ? fmaxf(acc, x[k]) : acc + x[k];
+        for (uint32_t k = 0; k < kGroup; ++k) a = is_max ? fmaxf(a, x[k]) : a + x[k];
+        __syncthreads();
+        sum[grp][col] = a;
+        __syncthreads();
+        if (grp == 0)
+#pragma unroll
+            for (uint32_t k = 0; k < kGroup; ++k) acc = is_max ? fmaxf(acc, sum[k][col]) : acc + sum[k][col];
     }
-    if (j < 0) {
-        grad[p] = acc;
+    if (threadIdx.x >= 64u) return;
+    if (!stats) {
+        if (grp == 0 && on) {
+            grad[p] = acc;
+            if (ADAM) adam(m, p, acc, lr, c1, c2);
+        }
         return;
     }
-    const uint32_t valid = hdr[0];
+    const uint32_t valid = valid_count(hdr);
+    const float den = __shfl(acc, kStErrDen, 64);
+    if (grp != 0 || !on) return;
     const float ntot = (float)max(valid, 1u) * 3.0f;
+    const int j = (int)col;
     if (j == kStLoss) {
         m.state[GI_MLP_STATE_LOSS] = __float_as_uint(acc / ntot);
         m.state[GI_MLP_STATE_VALID] = valid;
     } else if (j == kStErrNum) {
-        float den = 0.0f;
-        for (uint32_t w = 0; w < nwg; w += kGroup) den += part[(size_t)w * kPartStride + kParams + kStErrDen];
         m.state[GI_MLP_STATE_BATCH_ERR] = __float_as_uint(den > 0.0f ? acc / den : (acc > 0.0f ? kFltMax : 0.0f));
     } else if (j == kStNonFinite) {
         m.state[GI_MLP_STATE_NONFINITE] = (uint32_t)acc;
@@ -1069,40 +1142,7 @@ __global__ void __launch_bounds__(256) k_mlp_reduce(gi_mlp m, uint32_t nwg, cons
 __global__ void __launch_bounds__(256) k_mlp_adam(gi_mlp m, const float *grad, float lr, float c1, float c2)
 {
     const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= kParams) return;
-    const float g = grad[p];
-    const float mm = 0.9f * m.adam_m[p] + 0.1f * g;
-    const float vv = 0.99f * m.adam_v[p] + 0.01f * g * g;
-    m.adam_m[p] = mm;
-    m.adam_v[p] = vv;
-    const float np = m.params[p] - lr * (mm * c1) / (sqrtf(vv * c2) + 1e-8f);
-    m.params[p] = np;
-    if (m.ema) m.ema[p] = m.ema_decay * m.ema[p] + (1.0f - m.ema_decay) * np;
-}
-
-// usability after step t (one workgroup of 1024 threads)
-__global__ void __launch_bounds__(1024) k_mlp_state(gi_mlp m, uint32_t t)
-{
-    __shared__ uint32_t red[16];
-    // all of a thread's loads in flight at once
-    uint32_t bad = 0;
-    constexpr int kPer = (kParams + 1023) / 1024;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int p = threadIdx.x + 1024 * k;
-        if (p < kParams) bad += __builtin_isfinite(m.params[p]) ? 0u : 1u;
-    }
-    const uint32_t nonfinite = block_sum_1024(bad, red);
-    if (threadIdx.x == 0) {
-        const float be = __uint_as_float(m.state[GI_MLP_STATE_BATCH_ERR]);
-        const float old = __uint_as_float(m.state[GI_MLP_STATE_EMA_ERR]);
-        const float ema = t <= 1u ? be : 0.9f * old + 0.1f * be;
-        const bool ok = t >= m.warmup_steps && m.state[GI_MLP_STATE_NONFINITE] == 0u && ema <= m.max_rel_err &&
-                        nonfinite == 0u;
-        m.state[GI_MLP_STATE_STEPS] = t;
-        m.state[GI_MLP_STATE_EMA_ERR] = __float_as_uint(ema);
-        m.state[GI_MLP_STATE_USABLE] = ok ? 1u : 0u;
-    }
+    if (p < kParams) adam(m, p, grad[p], lr, c1, c2);
 }
 
 constexpr uint32_t train_wgs(uint32_t n) { return (n + kMS - 1) / kMS; }
@@ -1142,13 +1182,15 @@ gi_status scratch_address(void **out)
     return GI_OK;
 }
 
-gi_status prepare(const gi_mlp &m, hipStream_t st)
+// the inference operands; step > 0: after that optimiser step, with its state
+gi_status prepare(const gi_mlp &m, uint32_t step, hipStream_t st)
 {
+    const uint32_t more = step ? 1u : 0u;
     if (m.precision == GI_MLP_BF16) {
-        k_mlp_prepare_bf16<<<(kFrags * 64 * 8 + 255) / 256, 256, 0, st>>>(m);
+        k_mlp_prepare_bf16<<<kPrepBf16 + more, kPrepBlock, 0, st>>>(m, step);
     } else {
-        k_mlp_wscale<<<kLayers, 256, 0, st>>>(m);
-        k_mlp_prepare_fp8<<<(kFp8Frags * 64 * 32 + 255) / 256, 256, 0, st>>>(m);
+        k_mlp_wscale<<<kLayers + more, kPrepBlock, 0, st>>>(m, step);
+        k_mlp_prepare_fp8<<<(kFp8Frags * 64 * 32 + 255) / 256, 256, 0, st>>>(m, step);
     }
     return launched_mlp();
 }
@@ -1160,37 +1202,36 @@ gi_status check_batch(uint32_t n, const float *pos4, const float *nrm4, const fl
     return GI_OK;
 }
 
+// the bias corrections of step t
+struct AdamStep {
+    float lr, c1, c2;
+    AdamStep(uint32_t t, float rate)
+        : lr(rate), c1((float)(1.0 / (1.0 - std::pow(0.9, (double)t)))), c2((float)(1.0 / (1.0 - std::pow(0.99, (double)t))))
+    {
+    }
+};
+
+// the gradient of a batch; with a step, that step of the optimiser too
 gi_status grad_launch(const gi_mlp &m, uint32_t n, const float *pos4, const float *nrm4, const float *target4,
-                      const float *qprobe4, float *grad, void *ws, hipStream_t st)
+                      const float *qprobe4, float *grad, void *ws, const AdamStep *step, hipStream_t st)
 {
     uint32_t *hdr = reinterpret_cast<uint32_t *>(ws);
     float *part = reinterpret_cast<float *>(ws) + kHdr + kPartStride;
     const uint32_t nwg = train_wgs(n);
-    k_mlp_count<<<1, 1024, 0, st>>>(n, reinterpret_cast<const float4 *>(target4), hdr);
     __bf16 *frags = reinterpret_cast<__bf16 *>(reinterpret_cast<uint8_t *>(ws) + train_frag_off(n));
-    if (nwg) {
-        k_mlp_train_frags<<<((kFwdFrags + kBwdFrags) * 64 * 8 + 255) / 256, 256, 0, st>>>(m, frags);
+    const uint32_t frag_wgs = nwg ? ((kFwdFrags + kBwdFrags) * 64 * 8 + 255) / 256 : 0u;
+    k_mlp_train_prep<<<kCountWgs + frag_wgs, 256, 0, st>>>(m, n, reinterpret_cast<const float4 *>(target4), hdr, frags);
+    if (nwg)
         k_mlp_fwdbwd_mfma<<<nwg, kMBlock, 0, st>>>(m, n, reinterpret_cast<const float4 *>(pos4),
                                                    reinterpret_cast<const float4 *>(nrm4),
                                                    reinterpret_cast<const float4 *>(target4),
                                                    reinterpret_cast<const float4 *>(qprobe4), hdr,
                                                    reinterpret_cast<const bf16x8 *>(frags), part);
-    }
-    const uint32_t cols = (kParams + kStats + 255) / 256;
-    if (nwg) k_mlp_reduce1<<<dim3(cols, (nwg + kGroup - 1) / kGroup), 256, 0, st>>>(nwg, part);
-    k_mlp_reduce<<<cols, 256, 0, st>>>(m, nwg, part, grad, hdr);
+    if (step)
+        k_mlp_reduce<true><<<kRedWgs, kRedCols * kGroup, 0, st>>>(m, nwg, part, grad, hdr, step->lr, step->c1, step->c2);
+    else
+        k_mlp_reduce<false><<<kRedWgs, kRedCols * kGroup, 0, st>>>(m, nwg, part, grad, hdr, 0.0f, 0.0f, 0.0f);
     return launched_mlp();
-}
-
-gi_status adam_launch(const gi_mlp &m, const float *grad, uint32_t t, float lr, hipStream_t st)
-{
-    const double c1 = 1.0 / (1.0 - std::pow(0.9, (double)t));
-    const double c2 = 1.0 / (1.0 - std::pow(0.99, (double)t));
-    k_mlp_adam<<<(kParams + 255) / 256, 256, 0, st>>>(m, grad, lr, (float)c1, (float)c2);
-    k_mlp_state<<<1, 1024, 0, st>>>(m, t);
-    gi_status s = launched_mlp();
-    if (s != GI_OK) return s;
-    return prepare(m, st);
 }
 
 }  // namespace
@@ -1235,14 +1276,14 @@ gi_status gi_mlp_init(const gi_mlp *mlp, uint64_t seed, void *stream)
     if ((s = check_mlp(mlp)) != GI_OK) return s;
     k_mlp_init<<<(kParams + 255) / 256, 256, 0, S(stream)>>>(*mlp, seed);
     if ((s = launched_mlp()) != GI_OK) return s;
-    return prepare(*mlp, S(stream));
+    return prepare(*mlp, 0u, S(stream));
 }
 
 gi_status gi_mlp_prepare(const gi_mlp *mlp, void *stream)
 {
     gi_status s;
     if ((s = check_mlp(mlp)) != GI_OK) return s;
-    return prepare(*mlp, S(stream));
+    return prepare(*mlp, 0u, S(stream));
 }
 
 gi_status gi_mlp_infer(const gi_mlp *mlp, uint32_t n, const float *pos4, const float *nrm4, float *out4,
@@ -1267,7 +1308,7 @@ gi_status gi_mlp_grad(const gi_mlp *mlp, uint32_t n, const float *pos4, const fl
     if ((s = check_batch(n, pos4, nrm4, target4)) != GI_OK) return s;
     if (!grad || !workspace) return GI_ERR_NULL;
     if (workspace_bytes < train_bytes(n)) return GI_ERR_SHAPE;
-    return grad_launch(*mlp, n, pos4, nrm4, target4, qprobe4, grad, workspace, S(stream));
+    return grad_launch(*mlp, n, pos4, nrm4, target4, qprobe4, grad, workspace, nullptr, S(stream));
 }
 
 gi_status gi_mlp_adam(const gi_mlp *mlp, const float *grad, uint32_t t, float lr, void *stream)
@@ -1276,7 +1317,10 @@ gi_status gi_mlp_adam(const gi_mlp *mlp, const float *grad, uint32_t t, float lr
     if ((s = check_mlp(mlp)) != GI_OK) return s;
     if (!grad) return GI_ERR_NULL;
     if (t < 1 || !(lr > 0.0f)) return GI_ERR_PARAM;
-    return adam_launch(*mlp, grad, t, lr, S(stream));
+    const AdamStep step(t, lr);
+    k_mlp_adam<<<(kParams + 255) / 256, 256, 0, S(stream)>>>(*mlp, grad, step.lr, step.c1, step.c2);
+    if ((s = launched_mlp()) != GI_OK) return s;
+    return prepare(*mlp, t, S(stream));
 }
 
 gi_status gi_mlp_train_step(const gi_mlp *mlp, uint32_t n, const float *pos4, const float *nrm4,
@@ -1290,8 +1334,9 @@ gi_status gi_mlp_train_step(const gi_mlp *mlp, uint32_t n, const float *pos4, co
     if (workspace_bytes < train_bytes(n)) return GI_ERR_SHAPE;
     if (t < 1 || !(lr > 0.0f)) return GI_ERR_PARAM;
     float *grad = reinterpret_cast<float *>(workspace) + kHdr;
-    if ((s = grad_launch(*mlp, n, pos4, nrm4, target4, qprobe4, grad, workspace, S(stream))) != GI_OK) return s;
-    return adam_launch(*mlp, grad, t, lr, S(stream));
+    const AdamStep step(t, lr);
+    if ((s = grad_launch(*mlp, n, pos4, nrm4, target4, qprobe4, grad, workspace, &step, S(stream))) != GI_OK) return s;
+    return prepare(*mlp, t, S(stream));
 }
 
 gi_status gi_mlp_train_step_noalloc(const gi_mlp *mlp, uint32_t n, const float *pos4, const float *nrm4,
@@ -1306,8 +1351,9 @@ gi_status gi_mlp_train_step_noalloc(const gi_mlp *mlp, uint32_t n, const float *
     void *ws = nullptr;
     if ((s = scratch_address(&ws)) != GI_OK) return s;
     float *grad = reinterpret_cast<float *>(ws) + kHdr;
-    if ((s = grad_launch(*mlp, n, pos4, nrm4, target4, qprobe4, grad, ws, S(stream))) != GI_OK) return s;
-    return adam_launch(*mlp, grad, t, lr, S(stream));
+    const AdamStep step(t, lr);
+    if ((s = grad_launch(*mlp, n, pos4, nrm4, target4, qprobe4, grad, ws, &step, S(stream))) != GI_OK) return s;
+    return prepare(*mlp, t, S(stream));
 }
 
 }  // extern "C"
