@@ -433,7 +433,7 @@ def quality(gi, sg, torch, cfg, frames, n_eval, ref_spp, n_seeds):
 # --------------------------------------------------------------------------
 PROBE_INITIAL = "k_initial_tile<false, 0, 512, true>"    # the probe form's initial pass (FP32 texels)
 # the probe form's other resampling kernels of the 1080p workload (scene in LDS, FP32 texels)
-REUSE_KERNELS = ("k_temporal<true, false>", "k_spatial<true, false, 5, 16u>", "k_shade<true, false, false, 0>")
+REUSE_KERNELS = ("k_temporal<true, false, 16u>", "k_spatial<true, false, 5, 16u>", "k_shade<true, false, false, 0, 16u>")
 SQ_SETS = {"sq1": "SQ_WAVES SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU "
                   "SQ_ACTIVE_INST_LDS SQ_INSTS_VMEM_RD",
            "sq2": "SQ_INSTS_VALU SQ_INSTS_LDS SQ_INSTS_SALU SQ_ACTIVE_INST_ANY SQ_THREAD_CYCLES_VALU TCC_HIT_sum "

@@ -62,11 +62,22 @@ dim3 striped_grid(uint32_t W, uint32_t H, uint32_t SW)
     return dim3(kXcds * sw * ty);
 }
 
+// the pixel of a lane of the passes of one thread per pixel: 16x16 tiles in
+// image order, wider ones in stripes
+template <uint32_t SW>
+__device__ __forceinline__ bool pass_pixel(uint32_t W, uint32_t H, uint32_t &px, uint32_t &py)
+{
+    if constexpr (SW == (uint32_t)kTile) return tile_pixel(W, H, px, py);
+    else return tile_pixel_striped<SW>(W, H, px, py, threadIdx.x);
+}
+
 dim3 tile_grid(uint32_t W, uint32_t H)
 {
     uint32_t tx = (W + kTile - 1) / kTile, ty = (H + kTile - 1) / kTile;
     return dim3(tx, ty);
 }
+
+dim3 pass_grid(uint32_t W, uint32_t H, uint32_t SW) { return SW == (uint32_t)kTile ? tile_grid(W, H) : striped_grid(W, H, SW); }
 
 struct GB {
     V3 pos;
@@ -1193,16 +1204,21 @@ __device__ __forceinline__ int reproject(const gi_camera &c, V3 x)
 
 // 8 waves per SIMD: the latency-bound gathers and walks gain more from
 // occupancy than they lose to a few spilled values
-template <bool LDS, bool GLOSSY>
-__global__ void __launch_bounds__(kBlock, 8)
+template <bool LDS, bool GLOSSY, uint32_t SW>
+__global__ void __launch_bounds__(SW * kTile, SW == 16u ? 8 : 6)
     k_temporal(gi_scene sc, gi_gbuffer gb, gi_gbuffer gbp, gi_camera cam_prev, gi_reservoirs cur,
                gi_reservoirs hist, gi_params pp, uint32_t m_hist_cap, gi_reservoirs out, uint64_t seed,
                uint32_t frame)
 {
-    using Acc = typename std::conditional<LDS, GeoLds, GeoGlobal>::type;
+    using Acc = typename std::conditional<SW != (uint32_t)kTile, GeoSmall, typename std::conditional<LDS, GeoLds, GeoGlobal>::type>::type;
     uint32_t px, py;
-    const bool inside = tile_pixel(gb.width, gb.height, px, py);
-    if (LDS) stage_scene(sc);
+    const bool inside = pass_pixel<SW>(gb.width, gb.height, px, py);
+    if constexpr (SW != (uint32_t)kTile) {
+        stage_small(sc);
+        __syncthreads();
+    } else if (LDS) {
+        stage_scene(sc);
+    }
     if (!inside) return;
     const Acc acc(sc);
     const uint32_t p = py * gb.width + px;
@@ -1466,15 +1482,20 @@ __device__ V3 shade_glossy(const gi_scene &sc, const G &acc, const gi_probes &pr
 // recursion, started with the footprint of the segment x -> y (density of
 // the BSDF mixture at x) and a_0 c = c |x_0 - x|^2 / (4 pi cos) from the camera.
 // The Lambertian kernel is held to 5 waves per SIMD (no spills).
-template <bool LDS, bool WS, bool GLOSSY, int TEX>
-__global__ void __launch_bounds__(kBlock, GLOSSY ? 1 : 5)
+template <bool LDS, bool WS, bool GLOSSY, int TEX, uint32_t SW>
+__global__ void __launch_bounds__(SW * kTile, GLOSSY ? 1 : SW == 16u ? 5 : 6)
     k_shade(gi_scene sc, gi_gbuffer gb, gi_probes pr, gi_reservoirs res, const float4 *resid, gi_params pp,
             float4 *img, const float4 *q, gi_mlp mlp, uint64_t seed, uint32_t frame)
 {
-    using Acc = typename std::conditional<LDS, GeoLds, GeoGlobal>::type;
+    using Acc = typename std::conditional<SW != (uint32_t)kTile, GeoSmall, typename std::conditional<LDS, GeoLds, GeoGlobal>::type>::type;
     uint32_t px, py;
-    const bool inside = tile_pixel(gb.width, gb.height, px, py);
-    if (LDS) stage_scene(sc);
+    const bool inside = pass_pixel<SW>(gb.width, gb.height, px, py);
+    if constexpr (SW != (uint32_t)kTile) {
+        stage_small(sc);
+        __syncthreads();
+    } else if (LDS) {
+        stage_scene(sc);
+    }
     if (!inside) return;
     const Acc acc(sc);
     const uint32_t p = py * gb.width + px;
@@ -1959,6 +1980,27 @@ void launch_initial_probe(const gi_scene *sc, const gi_gbuffer &gb, const gi_pro
         else kernel<false, T2><<<(grid), (block), 0, (stream)>>>(__VA_ARGS__);               \
     } while (0)
 
+// How the passes of one thread per pixel (temporal, shade) hold the scene: in
+// LDS for each 16x16 tile where four of them fit a CU; a larger one, in its
+// small form, shared by the 768 threads of a 48x16 tile, two of which fill a
+// CU; else in global memory.  3840x2160, 1024 primitives, global memory ->
+// wide tiles: shade 1.45 -> 1.06 ms, temporal 1.49 -> 1.37; 640x360: 81 -> 57
+// us, 125 -> 86.  (The small form in 16x16 tiles, 1920x1080, 256 primitives:
+// shade 232 us against 224, temporal 247 against 240.)  Glossy layers keep to
+// the first and the last: their walks hold too many registers for 768 threads.
+struct SceneTiles {
+    uint32_t lds;
+    bool wide;
+    explicit SceneTiles(const gi_scene *sc) : lds(scene_lds(sc)), wide(false)
+    {
+        if (lds || !sc->cell_start || sc->n_items == 0 || (sc->options & (GI_OPT_NO_LDS | GI_OPT_GLOSSY))) return;
+        const uint32_t b = lds_small_bytes(*sc);
+        if (b == 0u || b > kTileLds) return;
+        lds = b;
+        wide = true;
+    }
+};
+
 template <int KM, uint32_t SW, class... A>
 void launch_spatial_t(const gi_scene *sc, uint32_t lds, uint32_t W, uint32_t H, hipStream_t st, A... a)
 {
@@ -2117,8 +2159,16 @@ gi_status gi_resample_temporal(const gi_scene *scene, const gi_gbuffer *gb, cons
     // subsampling, Sec. 6) still take over their history
     const double capd = floor((double)params->m_cap * (double)(params->M + params->M_light));
     const uint32_t m_hist_cap = capd >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)capd;
-    GI_LAUNCH_LDS_G(k_temporal, glossy_scene(scene), tile_grid(W, H), kBlock, scene_lds(scene), S(stream), *scene,
-                    *gb, *gb_prev, *prev_cam, *cur_in, *history, *params, m_hist_cap, *out, seed, frame);
+    const SceneTiles st(scene);
+#define GI_TP(L, G, SW)                                                                                        \
+    k_temporal<L, G, SW><<<pass_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(*scene, *gb, *gb_prev, *prev_cam, *cur_in, \
+                                                                                    *history, *params, m_hist_cap, *out, seed, frame)
+    if (glossy_scene(scene)) {
+        if (st.lds) GI_TP(true, true, 16u); else GI_TP(false, true, 16u);
+    } else {
+        if (st.wide) GI_TP(true, false, 48u); else if (st.lds) GI_TP(true, false, 16u); else GI_TP(false, false, 16u);
+    }
+#undef GI_TP
     return launched();
 }
 
@@ -2162,20 +2212,21 @@ gi_status gi_shade(const gi_scene *scene, const gi_gbuffer *gb, const gi_probes 
     if (glossy && (!(params->foot_c >= 0.0f) || params->glossy_depth < 1u || params->glossy_depth > GI_MAX_GLOSSY_DEPTH))
         return GI_ERR_PARAM;
     if (W == 0 || H == 0) return GI_OK;
-    const uint32_t lds = scene_lds(scene);
-    const dim3 grid = tile_grid(W, H);
+    const SceneTiles st(scene);
     const float4 *rs = reinterpret_cast<const float4 *>(resid);
     float4 *img = reinterpret_cast<float4 *>(out_rgba);
     const bool f16 = probes->texel == GI_TEXEL_F16;
-#define GI_SH(L, G, T)                                                                                   \
-    k_shade<L, false, G, T><<<grid, kBlock, (L) ? lds : 0u, S(stream)>>>(*scene, *gb, *probes, *res, rs, *params, \
-                                                                          img, nullptr, gi_mlp{}, seed, frame)
+#define GI_SH(L, G, T, SW)                                                                                     \
+    k_shade<L, false, G, T, SW><<<pass_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(                    \
+        *scene, *gb, *probes, *res, rs, *params, img, nullptr, gi_mlp{}, seed, frame)
     if (glossy) {
-        if (lds) { if (f16) GI_SH(true, true, kTexF16); else GI_SH(true, true, kTexF32); }
-        else { if (f16) GI_SH(false, true, kTexF16); else GI_SH(false, true, kTexF32); }
+        if (st.lds) { if (f16) GI_SH(true, true, kTexF16, 16u); else GI_SH(true, true, kTexF32, 16u); }
+        else { if (f16) GI_SH(false, true, kTexF16, 16u); else GI_SH(false, true, kTexF32, 16u); }
+    } else if (st.wide) {
+        if (f16) GI_SH(true, false, kTexF16, 48u); else GI_SH(true, false, kTexF32, 48u);
     } else {
-        if (lds) { if (f16) GI_SH(true, false, kTexF16); else GI_SH(true, false, kTexF32); }
-        else { if (f16) GI_SH(false, false, kTexF16); else GI_SH(false, false, kTexF32); }
+        if (st.lds) { if (f16) GI_SH(true, false, kTexF16, 16u); else GI_SH(true, false, kTexF32, 16u); }
+        else { if (f16) GI_SH(false, false, kTexF16, 16u); else GI_SH(false, false, kTexF32, 16u); }
     }
 #undef GI_SH
     return launched();
@@ -2275,13 +2326,16 @@ gi_status gi_shade_mlp(const gi_scene *scene, const gi_gbuffer *gb, const gi_pro
                               reinterpret_cast<const float4 *>(res->n_wsum), q, true, S(stream))) != GI_OK)
         return s;
     {
-        const uint32_t lds = scene_lds(scene);
+        const SceneTiles st(scene);
         const float4 *rs = reinterpret_cast<const float4 *>(resid);
         float4 *img = reinterpret_cast<float4 *>(out_rgba);
-        if (lds) k_shade<true, true, false, kTexAny><<<tile_grid(W, H), kBlock, lds, S(stream)>>>(*scene, *gb, *probes, *res, rs,
-                                                                                      *params, img, q, *mlp, 0ull, 0u);
-        else k_shade<false, true, false, kTexAny><<<tile_grid(W, H), kBlock, 0, S(stream)>>>(*scene, *gb, *probes, *res, rs,
-                                                                                 *params, img, q, *mlp, 0ull, 0u);
+#define GI_SH(L, SW)                                                                                   \
+    k_shade<L, true, false, kTexAny, SW><<<pass_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(      \
+        *scene, *gb, *probes, *res, rs, *params, img, q, *mlp, 0ull, 0u)
+        if (st.wide) GI_SH(true, 48u);
+        else if (st.lds) GI_SH(true, 16u);
+        else GI_SH(false, 16u);
+#undef GI_SH
     }
     return launched();
 }
