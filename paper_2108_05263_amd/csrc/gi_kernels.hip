@@ -1269,23 +1269,38 @@ struct RayPool {
 // The rays that only decide Z are cast whether or not x sees the sample; W is
 // zero if it does not.  74 VGPRs, 5 waves per SIMD (4 with glossy layers, 6
 // for the 768-thread tiles).
+// The pixel of slot k of a tile: 8x8 pixels for 256 threads (SW = 8, tiles in
+// image order), else SW x 16 in stripes.
+template <uint32_t SW>
+__device__ __forceinline__ bool spatial_pixel(uint32_t W, uint32_t H, uint32_t &px, uint32_t &py, uint32_t k)
+{
+    if constexpr (SW == 8u) {
+        const uint32_t tx = (W + 7u) / 8u;
+        px = (blockIdx.x % tx) * 8u + (k & 7u);
+        py = (blockIdx.x / tx) * 8u + (k >> 3);
+        return px < W && py < H;
+    } else {
+        return tile_pixel_striped<SW>(W, H, px, py, k);
+    }
+}
+
 template <bool LDS, bool GLOSSY, int KM, uint32_t SW>
-__global__ void __launch_bounds__(SW * kTile, SW == 16u ? (GLOSSY ? 4 : 5) : 6)
+__global__ void __launch_bounds__(SW == 8u ? 256u : SW * kTile, SW == 48u ? 6 : GLOSSY ? 4 : 5)
     k_spatial(gi_scene sc, gi_gbuffer gb, gi_reservoirs in, gi_params pp, uint32_t pass, gi_reservoirs out,
               uint64_t seed, uint32_t frame)
 {
-    constexpr int NT = (int)SW * kTile;
+    constexpr int NT = SW == 8u ? 256 : (int)SW * kTile, NP = SW == 8u ? 64 : NT;
     using Acc = typename std::conditional<LDS, GeoSmall, GeoGlobal>::type;
     uint32_t px, py;
-    const bool inside = tile_pixel_striped<SW>(gb.width, gb.height, px, py, threadIdx.x);
+    const bool inside = (NP == NT || threadIdx.x < (uint32_t)NP) && spatial_pixel<SW>(gb.width, gb.height, px, py, threadIdx.x);
     if (LDS) stage_small(sc);
     const Acc acc(sc);
     const uint32_t W = gb.width, H = gb.height, t = threadIdx.x;
     const uint32_t p = py * W + px;
     char *const lds = reinterpret_cast<char *>(gi_lds) + (LDS ? lds_small_bytes(sc) : 0u);
-    RayPool<KM, NT> &pool = *reinterpret_cast<RayPool<KM, NT> *>(lds);
+    RayPool<KM, NP> &pool = *reinterpret_cast<RayPool<KM, NP> *>(lds);
     if (t < kBins) pool.hist[t] = 0u;
-    pool.seen[t] = 0u;
+    if (NP == NT || t < (uint32_t)NP) pool.seen[t] = 0u;
 
     float ph = 0.0f, wsum = 0.0f;
     uint32_t Msum = 0u;
@@ -1394,7 +1409,7 @@ __global__ void __launch_bounds__(SW * kTile, SW == 16u ? (GLOSSY ? 4 : 5) : 6)
     for (uint32_t at = t; at < pool.hist[kBins]; at += NT) {
         const uint32_t e = pool.order[at], k = e & 0xFFFu, j = e >> 12;
         uint32_t kx, ky;
-        tile_pixel_striped<SW>(W, H, kx, ky, k);
+        spatial_pixel<SW>(W, H, kx, ky, k);
         const uint32_t pk = ky * W + kx, q = j == 0u ? pk : pool.q[j - 1u][k];
         const GB d = load_gb<false>(gb, q);
         // the sample as its pixel has written it (the barriers order this
@@ -2004,14 +2019,15 @@ struct SceneTiles {
 template <int KM, uint32_t SW, class... A>
 void launch_spatial_t(const gi_scene *sc, uint32_t lds, uint32_t W, uint32_t H, hipStream_t st, A... a)
 {
-    const uint32_t bytes = lds + (uint32_t)sizeof(RayPool<KM, (int)SW * kTile>), nt = SW * kTile;
-    const dim3 grid = striped_grid(W, H, SW);
+    constexpr uint32_t nt = SW == 8u ? 256u : SW * kTile, np = SW == 8u ? 64u : nt;
+    const uint32_t bytes = lds + (uint32_t)sizeof(RayPool<KM, (int)np>);
+    const dim3 grid = SW == 8u ? dim3(((W + 7u) / 8u) * ((H + 7u) / 8u)) : striped_grid(W, H, SW);
     if (glossy_scene(sc)) {
         if (lds) k_spatial<true, true, KM, SW><<<grid, nt, bytes, st>>>(a...);
-        else if constexpr (SW == 16u) k_spatial<false, true, KM, SW><<<grid, nt, bytes, st>>>(a...);
+        else if constexpr (SW != 48u) k_spatial<false, true, KM, SW><<<grid, nt, bytes, st>>>(a...);
     } else {
         if (lds) k_spatial<true, false, KM, SW><<<grid, nt, bytes, st>>>(a...);
-        else if constexpr (SW == 16u) k_spatial<false, false, KM, SW><<<grid, nt, bytes, st>>>(a...);
+        else if constexpr (SW != 48u) k_spatial<false, false, KM, SW><<<grid, nt, bytes, st>>>(a...);
     }
 }
 
@@ -2020,11 +2036,22 @@ void launch_spatial_t(const gi_scene *sc, uint32_t lds, uint32_t W, uint32_t H, 
 // is shared by the 768 threads of a 48x16 tile, two of which fill a CU
 // (3840x2160, 1024 primitives: 2.87 ms, from global memory 3.76, shared by
 // 256 threads 5.18, by 512 3.85).
+//
+// An image of few pixels leaves most of the chip idle, and six rays in a row
+// per thread are its time: tiles of 8x8 pixels share their rays between 256
+// threads (two rounds of the pool instead of six).  64x64, 16x16 -> 8x8 tiles:
+// 8 primitives 41 -> 20 us, 256: 50 -> 36, 1024 (from global memory): 49 -> 46;
+// 320x180: 41 -> 22, 57 -> 43, 74 -> 64; from 480x270 on the waves without
+// pixels cost as much as they gain (44 -> 46, 91 -> 77, 97 -> 85; 640x360: 56
+// -> 60, 114 -> 108, 133 -> 130).
+constexpr uint64_t kSmallImage = 65536u;
+
 template <int KM, class... A>
 void launch_spatial(const gi_scene *sc, uint32_t W, uint32_t H, hipStream_t st, A... a)
 {
     const uint32_t lds = sc->cell_start && sc->n_items && !(sc->options & GI_OPT_NO_LDS) ? lds_small_bytes(*sc) : 0u;
-    if (lds && lds + sizeof(RayPool<KM, 256>) <= kLdsScene) launch_spatial_t<KM, 16u>(sc, lds, W, H, st, a...);
+    if ((uint64_t)W * H <= kSmallImage) launch_spatial_t<KM, 8u>(sc, lds + sizeof(RayPool<KM, 64>) <= kLdsScene ? lds : 0u, W, H, st, a...);
+    else if (lds && lds + sizeof(RayPool<KM, 256>) <= kLdsScene) launch_spatial_t<KM, 16u>(sc, lds, W, H, st, a...);
     else if (lds && lds + sizeof(RayPool<KM, 768>) <= kTileLds) launch_spatial_t<KM, 48u>(sc, lds, W, H, st, a...);
     else launch_spatial_t<KM, 16u>(sc, 0u, W, H, st, a...);
 }
