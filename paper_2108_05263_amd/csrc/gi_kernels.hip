@@ -1247,6 +1247,94 @@ __global__ void __launch_bounds__(SW * kTile, SW == 16u ? 8 : 6)
     store_res(out, p, finish<GLOSSY>(sc, acc, m, g, Mdom, [&](int) { return load_gb<GLOSSY>(gbp, qprev); }, pp));
 }
 
+// The temporal pass of an image of few pixels: an 8x8 tile's two rays per
+// pixel go to a wave each instead of one after the other, and the tiles to four
+// times as many CUs.  Bound by the latency of one walk; k_temporal -> this:
+// 64x64, 8 primitives 27 -> 16 us; 99x50, 256 primitives 62 -> 34; 320x180
+// 65 -> 34, 1024 primitives 79 -> 54.  (The second ray is cast whether or not
+// x sees the sample; W is zero if it does not.)
+template <bool LDS>
+__global__ void __launch_bounds__(128)
+    k_temporal_small(gi_scene sc, gi_gbuffer gb, gi_gbuffer gbp, gi_camera cam_prev, gi_reservoirs cur,
+                     gi_reservoirs hist, gi_params pp, uint32_t m_hist_cap, gi_reservoirs out, uint64_t seed,
+                     uint32_t frame)
+{
+    using Acc = typename std::conditional<LDS, GeoLds, GeoGlobal>::type;
+    __shared__ uint32_t prev[64], seen[64];      // the pixel whose ray the second wave casts (~0: none), its answer
+    const uint32_t t = threadIdx.x & 63u, tx = (gb.width + 7u) / 8u;
+    const bool first = threadIdx.x < 64u;
+    const uint32_t px = (blockIdx.x % tx) * 8u + (t & 7u), py = (blockIdx.x / tx) * 8u + (t >> 3);
+    const bool inside = px < gb.width && py < gb.height;
+    const uint32_t p = py * gb.width + px;
+    if (LDS) stage_scene(sc);
+    const Acc acc(sc);
+    bool have = false, ray = false;
+    float wsum = 0.0f, ph = 0.0f;
+    uint32_t M0 = 0u, M1 = 0u, Msum = 0u, q1 = ~0u;
+    const auto merge = [&] {
+        const GB g = load_gb<false>(gb, p);
+        const Res rc = load_res(cur, p);
+        if (!active<false>(g)) {
+            store_res(out, p, rc);
+            return;
+        }
+        Merge m{0.0f, 0u, false, rc};
+        M0 = rc.M;
+        uint32_t qprev = 0u;
+        merge_in<false>(m, g, rc, rc.M, 0.0f, pp.g_max);
+        const int q = reproject(cam_prev, g.pos);
+        if (q >= 0) {
+            const GB gq = load_gb<false>(gbp, (uint32_t)q);
+            if (similar(g, gq, pp)) {
+                const Res rh = load_res(hist, (uint32_t)q);
+                M1 = min(rh.M, m_hist_cap);
+                const uint4 rn = philox(seed, p, frame, kPassTemporal, 0u);
+                merge_in<false>(m, g, rh, M1, u01(rn.x), pp.g_max);
+                qprev = (uint32_t)q;
+            }
+        }
+        have = m.have;
+        wsum = m.wsum;
+        Msum = m.Msum;
+        Res r = m.sel;
+        if (!have) r = empty_res(Msum);
+        r.wsum = wsum;
+        r.M = Msum;
+        if (have) {
+            ph = res_target<false>(g, r, pp.g_max);
+            r.W = 0.0f;
+            ray = pp.unbiased && ph > 0.0f;
+            if (ray && M1 != 0u && res_target<false>(load_gb<false>(gbp, qprev), r, pp.g_max) > 0.0f) q1 = qprev;
+        }
+        store_res(out, p, r);
+    };
+    if (first) {
+        if (inside) merge();
+        prev[t] = q1;
+    }
+    __syncthreads();
+    // the sample as its pixel has written it (the barrier orders this
+    // workgroup's writes before its reads)
+    const uint32_t q = first ? p : prev[t];
+    bool vis = false;
+    if (first ? ray : q != ~0u) {
+        const GB d = load_gb<false>(first ? gb : gbp, q);
+        const V3 y = xyz(reinterpret_cast<const float4 *>(out.y_W)[p]), n = xyz(reinterpret_cast<const float4 *>(out.n_wsum)[p]);
+        vis = visible(sc, acc, d.pos, d.n, y, n, is_zero(n));
+    }
+    if (!first) seen[t] = vis ? 1u : 0u;
+    __syncthreads();
+    if (!first || !have) return;
+    float W = 0.0f;
+    if (pp.unbiased) {
+        const uint32_t z = M0 + (seen[t] ? M1 : 0u);
+        if (vis && z > 0u) W = wsum * rcp((float)z * ph);
+    } else if (Msum > 0u && ph > 0.0f) {
+        W = wsum * rcp((float)Msum * ph);
+    }
+    out.y_W[4u * (size_t)p + 3u] = W;
+}
+
 // The visibility rays of a workgroup's pixels: up to KM + 1 of each, sorted
 // by direction cell, so that all lanes of a wave walk and walk together.
 template <int KM, int NT>
@@ -2186,6 +2274,14 @@ gi_status gi_resample_temporal(const gi_scene *scene, const gi_gbuffer *gb, cons
     // subsampling, Sec. 6) still take over their history
     const double capd = floor((double)params->m_cap * (double)(params->M + params->M_light));
     const uint32_t m_hist_cap = capd >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)capd;
+    // few pixels, where the spatial pass takes small tiles too (Lambertian
+    // scenes: the glossy target has no form of its own there)
+    if ((uint64_t)W * H <= kSmallImage && !glossy_scene(scene)) {
+        const uint32_t lds = scene_lds(scene);
+        GI_LAUNCH_LDS(k_temporal_small, dim3(((W + 7u) / 8u) * ((H + 7u) / 8u)), 128, lds, S(stream), *scene, *gb, *gb_prev,
+                      *prev_cam, *cur_in, *history, *params, m_hist_cap, *out, seed, frame);
+        return launched();
+    }
     const SceneTiles st(scene);
 #define GI_TP(L, G, SW)                                                                                        \
     k_temporal<L, G, SW><<<pass_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(*scene, *gb, *gb_prev, *prev_cam, *cur_in, \
