@@ -1984,17 +1984,23 @@ bool tile_form(const gi_scene *sc, const gi_params *pp, uint32_t W, uint32_t H)
     return pp->M >= 24u || px >= 900000u || (px <= 96000u && 256u * pp->M >= 3u * sc->n_prims);
 }
 
+// An image of so few pixels leaves most of the chip idle to the forms of one
+// thread per pixel.
+constexpr uint64_t kSmallImage = 65536u;
+
 // Where the learned-cache form traces its candidates by tiles.  The walks it
 // replaces cost less than the probe form's pixels, so fewer frames gain: with
 // 256 primitives from M = 8 on (1920x1080: M = 32 5.69 -> 4.46 ms, M = 13
 // 2.33 -> 1.97, M = 8 1.47 -> 1.26, whole pass; 64x36, M = 32: 765 -> 234 us;
 // M = 4 0.81 -> 0.84); with 1024 the lists are longer and leave room for half
-// the rays per round, and only M = 32 gains (1920x1080 8.31 -> 7.91 ms; M = 13
-// 3.38 -> 3.72).
-bool cand_tiles(const gi_scene *sc, const gi_params &pp)
+// the rays per round, and of large images only M = 32 gains (1920x1080 8.31 ->
+// 7.91 ms; M = 13 3.38 -> 3.72); of small ones, which the pixel form does not
+// spread over the chip, all do (238x121, M = 13: 556 -> 337 us; 320x200, M = 8:
+// 362 -> 300; 64x36, M = 8: 321 -> 215).
+bool cand_tiles(const gi_scene *sc, const gi_params &pp, uint32_t W, uint32_t H)
 {
     if (sc->n_prims > kListMaxPrims || (sc->options & GI_OPT_NO_LDS) != 0u) return false;
-    return pp.M >= (sc->n_prims > 512u ? 24u : 8u);
+    return pp.M >= (sc->n_prims > 512u && (uint64_t)W * H > kSmallImage ? 24u : 8u);
 }
 
 bool glossy_scene(const gi_scene *sc) { return (sc->options & GI_OPT_GLOSSY) != 0u; }
@@ -2040,17 +2046,19 @@ void launch_cand(const gi_scene *sc, const gi_gbuffer &gb, const gi_params &pp, 
                  uint32_t frame, const gi_mlp &mlp, hipStream_t st)
 {
     const uint32_t W = gb.width, H = gb.height, lds = scene_lds(sc);
-    if (!cand_tiles(sc, pp)) {
+    if (!cand_tiles(sc, pp, W, H)) {
         GI_LAUNCH_LDS(k_cand, tile_grid(W, H), kBlock, lds, st, *sc, gb, pp, ws, seed, frame, mlp);
         return;
     }
     // Some 4000 rays per tile, which two rounds trace; less, but not below
-    // 1000, where the image would not make 2048 tiles.  1920x1080: M = 32
+    // 1000 (500 where a round holds half as many), where the image would not
+    // make 2048 tiles.  1920x1080: M = 32
     // 16x8 4.46 ms (16x16 4.42, 32x16 4.64, 8x8 4.79), M = 13 16x16 1.97
     // (16x8 2.13), M = 8 32x16 1.26 (16x16 1.29, 16x8 1.56); 320x180, M = 32:
     // 8x8 299 us, 16x8 419, 16x16 679.
     uint32_t lw = pp.M >= 12u ? 4u : 5u, lh = pp.M >= 24u ? 3u : 4u;
-    while (lw + lh > 6u && (pp.M << (lw + lh - 1u)) >= 1024u &&
+    const uint32_t least = sc->n_prims > 512u ? 512u : 1024u;
+    while (lw + lh > 6u && (pp.M << (lw + lh - 1u)) >= least &&
            (uint64_t)((W + (1u << lw) - 1u) >> lw) * ((H + (1u << lh) - 1u) >> lh) < 2048u) {
         if (lw > lh) --lw;
         else --lh;
@@ -2132,7 +2140,6 @@ void launch_spatial_t(const gi_scene *sc, uint32_t lds, uint32_t W, uint32_t H, 
 // 320x180: 41 -> 22, 57 -> 43, 74 -> 64; from 480x270 on the waves without
 // pixels cost as much as they gain (44 -> 46, 91 -> 77, 97 -> 85; 640x360: 56
 // -> 60, 114 -> 108, 133 -> 130).
-constexpr uint64_t kSmallImage = 65536u;
 
 template <int KM, class... A>
 void launch_spatial(const gi_scene *sc, uint32_t W, uint32_t H, hipStream_t st, A... a)

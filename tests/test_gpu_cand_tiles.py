@@ -31,6 +31,8 @@ pytestmark = [pytest.mark.gpu,
     ("uhd", 323, 181, 24, "always", 0),
     ("uhd", 1027, 519, 32, "always", 0),
     ("uhd", 90, 50, 23, "always", 0),
+    ("uhd", 90, 50, 8, "always", 0),
+    ("uhd", 257, 256, 13, "always", 0),        # past the small images' rule: both sides are the pixel form
 ])
 def test_cand_tiles_are_the_pixel_form(room, W, H, M, mode, m_light):
     from paper_2108_05263_amd import gi
