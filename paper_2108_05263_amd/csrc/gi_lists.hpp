@@ -27,6 +27,7 @@ constexpr int kBinSide = 12;
 constexpr int kBins = kBinSide * kBinSide;
 constexpr uint32_t kListMaxPrims = 1024u;
 constexpr int kListBuckets = 32;     // distance classes the primitives are ordered by
+constexpr float kListFar = 1e18f;     // largest distance: the squares behind it stay finite
 
 // 32-slot words of the lists: spheres fill the first ones, boxes the rest
 // (so two of them may be partly filled); even, since a wave writes two
@@ -107,7 +108,8 @@ __device__ __forceinline__ float4 bin_cone(int b)
 //  - A primitive is kept for a cell unless a plane through the cone's apex
 //    separates it, the origin box added to its extent, from the cone: the
 //    tangent plane of the cone toward the primitive's centre, or the plane
-//    behind the apex.
+//    behind the apex.  Where a bound is no number (an infinite slab has no
+//    centre) it stays; sizes count by their absolute values, as in the tests.
 template <int NT>
 __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Box3 org, Box3 nrm, uint32_t *scratch)
 {
@@ -144,12 +146,12 @@ __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Bo
         const float4 a = src[4u * i], b = src[4u * i + 1u];
         geo_records(a, b, ga[k], gb[k]);
         cls[k] = __float_as_uint(a.w) == 0u ? 0u : 1u;
-        const V3 v = vabs(xyz(a) - org.c), e = cls[k] ? xyz(b) : v3(0.0f, 0.0f, 0.0f);
+        const V3 v = vabs(xyz(a) - org.c), e = cls[k] ? vabs(xyz(b)) : v3(0.0f, 0.0f, 0.0f);
         const V3 q = v3(fmaxf(v.x - org.h.x - e.x, 0.0f), fmaxf(v.y - org.h.y - e.y, 0.0f),
                         fmaxf(v.z - org.h.z - e.z, 0.0f));
-        const float d = fsqrt(dot(q, q)) - (cls[k] ? 0.0f : b.x);
+        const float d = fsqrt(dot(q, q)) - (cls[k] ? 0.0f : fabsf(b.x));
         const float slop = 1e-4f * (fabsf(a.x) + fabsf(a.y) + fabsf(a.z) + fabsf(org.c.x) + fabsf(org.c.y) + fabsf(org.c.z));
-        dist[k] = fmaxf(0.0f, fmaf(d, 0.999f, -slop));
+        dist[k] = fminf(fmaxf(0.0f, fmaf(d, 0.999f, -slop)), kListFar);
         far = fmaxf(far, dist[k]);
     }
 #pragma unroll
@@ -241,8 +243,8 @@ __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Bo
         }
         const float slop = 1e-4f * (fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(org.c.x) + fabsf(org.c.y) + fabsf(org.c.z));
         v = v - org.c;
-        h = 1.001f * (h + org.h);
-        rad = valid ? fmaf(rad, 1.001f, slop) : -kInf;     // an empty slot is behind every cone
+        h = 1.001f * (vabs(h) + org.h);
+        rad = valid ? 1.001f * fabsf(rad) + slop : -kInf;  // an empty slot is behind every cone
         const float vv = dot(v, v);
         for (uint32_t u0 = part * kIlp; u0 < used; u0 += parts * kIlp) {
             float4 cn[kIlp];
@@ -269,7 +271,7 @@ __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Bo
             uint32_t c_k = 0u;
 #pragma unroll
             for (uint32_t k = 0; k < kIlp; ++k) {
-                const uint64_t b = __builtin_amdgcn_ballot_w64(fminf(side[k], back[k]) >= 0.0f);
+                const uint64_t b = __builtin_amdgcn_ballot_w64(!(fminf(side[k], back[k]) < 0.0f));
                 if (lane == k) {
                     keep = b;
                     c_k = __float_as_uint(cs[k].y);
