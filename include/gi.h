@@ -127,7 +127,12 @@ typedef struct gi_camera {
  *   0xFFFF = miss), albedo 8-byte records (half r, g, b, 0); pos_depth and
  *   emit stay float4; readers renormalise the half-precision normal.  Scenes
  *   must have fewer than 65535 - 6 primitives.
- * A pixel whose primary ray leaves the scene has prim = GI_MISS and emit = sky. */
+ * A pixel whose primary ray leaves the scene has prim = GI_MISS and emit = sky.
+ * Normals are meant to be of unit length.  A normal of another length gives
+ * the candidate rays formed about it directions of other lengths, which the
+ * sphere test takes for unit ones: those rays find the closest hit of the
+ * brute-force loop, or, where the initial pass walks the grid, one that may
+ * depend on the grid's cells. */
 typedef struct gi_gbuffer {
     uint32_t width, height;
     float *pos_depth;

@@ -78,6 +78,19 @@ struct Box3 {
     V3 c, h;                // centre and half extents
 };
 
+// What the lists take for granted of a pixel's rays: that they start at a
+// point, and that their directions are of unit length to within 1e-3 (a frame
+// about a normal with |n|^2 within 2e-4 of 1 keeps them to 2e-4, a lobe's half
+// vector to 8e-4), so that a ray parameter is a distance at least to the 1e-3
+// that the lists' distances are lowered by.  A pixel without either counts as
+// far away instead.  The origins' box then reaches every primitive, and every
+// cell lists it; the normals' box shows it, and no word lies beyond a hit
+// (what the cells leave out still lies off the ray, whatever its length).  Its
+// rays find what the brute-force loop finds.
+__device__ __forceinline__ V3 far_point() { return v3(kListFar, kListFar, kListFar); }
+__device__ __forceinline__ V3 list_origin(V3 o) { return fabsf(o.x) + fabsf(o.y) + fabsf(o.z) < kInf ? o : far_point(); }
+__device__ __forceinline__ V3 list_axis(V3 n) { return fabsf(dot(n, n) - 1.0f) <= 2e-4f ? n : far_point(); }
+
 __device__ __forceinline__ V3 vabs(V3 a) { return v3(fabsf(a.x), fabsf(a.y), fabsf(a.z)); }
 
 // Bounding cone (axis, cos) of direction cell b.  A cell is one planar patch
@@ -115,6 +128,8 @@ __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Bo
 {
     constexpr uint32_t kPer = kListMaxPrims / NT, kWaves = NT / 64;
     const uint32_t t = threadIdx.x, n = sc.n_prims;
+    const bool unit = nrm.c.x + nrm.h.x < 2.0f;            // no list_axis was far away
+    const float lower = unit ? 0.999f : 0.0f;
     // the cells in use: cone axis and cos, then sin and the cell
     float4 *cone = reinterpret_cast<float4 *>(scratch);
     float2 *cell = reinterpret_cast<float2 *>(scratch + 4 * kBins);
@@ -128,7 +143,7 @@ __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Bo
         const V3 a = v3(c.x, c.y, c.z);
         const float st = fsqrt(fmaxf(0.0f, fmaf(-c.w, c.w, 1.0f)));
         // no ray into a cell below every surface: largest n.d over the box and the cone
-        if (dot(nrm.c, a) + dot(nrm.h, vabs(a)) >= -st - 1e-2f) {
+        if (!unit || dot(nrm.c, a) + dot(nrm.h, vabs(a)) >= -st - 1e-2f) {
             const uint32_t u = atomicAdd(&dmax[1], 1u);
             cone[u] = c;
             cell[u] = make_float2(st, __uint_as_float(t));
@@ -151,7 +166,7 @@ __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Bo
                         fmaxf(v.z - org.h.z - e.z, 0.0f));
         const float d = fsqrt(dot(q, q)) - (cls[k] ? 0.0f : fabsf(b.x));
         const float slop = 1e-4f * (fabsf(a.x) + fabsf(a.y) + fabsf(a.z) + fabsf(org.c.x) + fabsf(org.c.y) + fabsf(org.c.z));
-        dist[k] = fminf(fmaxf(0.0f, fmaf(d, 0.999f, -slop)), kListFar);
+        dist[k] = fminf(fmaxf(0.0f, fmaf(d, lower, -slop)), kListFar);
         far = fmaxf(far, dist[k]);
     }
 #pragma unroll
@@ -187,7 +202,7 @@ __device__ __forceinline__ void build_lists(const gi_scene &sc, TileLists &L, Bo
     L.nw = L.sw + ((n - ns + 31u) >> 5);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63u;
     // every cell starts with every primitive: what a ray into a cell not in
-    // use meets (only from a normal that is not of unit length)
+    // use meets
     if (lane < L.nw) {
         const uint32_t first = lane < L.sw ? 32u * lane : 32u * (lane - L.sw), left = (lane < L.sw ? ns : n - ns) - first;
         const uint32_t all = left >= 32u ? ~0u : (1u << left) - 1u;

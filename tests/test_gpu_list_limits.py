@@ -63,3 +63,25 @@ def test_odd_primitives_stay_in_the_lists(kind, form):
     assert odd.any(), "the odd primitives are hit"
     for a, b in zip(lists, brute):
         assert torch.equal(a, b), f"{int((a != b).sum())} words differ"
+
+
+def _odd_pixels(gb):
+    gb.nrm_prim[::3, :3] *= -0.5
+    gb.nrm_prim[1::7, :3] *= 3.0
+    gb.nrm_prim[5::90, :3] *= 1.01            # a tile's only one
+    gb.nrm_prim[77, 1] = float("nan")
+    gb.pos_depth[123, 0] = float("inf")
+    gb.pos_depth[2345, 2] = float("nan")
+
+
+# normals of other lengths (directions of other lengths, for which the ray
+# parameter is no distance) and pixels without a place
+@pytest.mark.parametrize("form", ["probe", "cache"])
+@pytest.mark.parametrize("open_", [False, True])
+def test_odd_pixels_find_the_brute_force_hits(open_, form):
+    scene = sg.make_scene(CFG)
+    if open_:
+        scene = dataclasses.replace(scene, has_room=False, sky=np.array([1.0, 2.0, 3.0], np.float32))
+    lists, brute = (_planes(form, scene, 90, 50, 32, lds, _odd_pixels) for lds in (True, False))
+    for a, b in zip(lists, brute):
+        assert torch.equal(a, b), f"{int((a != b).sum())} words differ"
