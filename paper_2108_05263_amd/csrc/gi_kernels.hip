@@ -28,20 +28,29 @@ constexpr uint32_t kSelBytes = 64u;   // k_initial's per-thread slot: selected c
 // Workgroups are dealt round-robin to the chip's 8 XCDs, each with its own L2
 constexpr uint32_t kXcds = 8;
 
+// The pixel of a lane of the passes of one thread per pixel: SW x 16 tiles in
+// image order.  (48x16 tiles in stripes left XCDs without work where tile
+// columns are few: 40x2000, 1024 primitives, shade 102 us, in image order 45;
+// 1283x721 177 and 162; 3840x2160 1.28 and 1.25 ms.)
+template <uint32_t SW = (uint32_t)kTile>
 __device__ __forceinline__ bool tile_pixel(uint32_t W, uint32_t H, uint32_t &px, uint32_t &py)
 {
-    uint32_t t = threadIdx.x, w = t >> 6, l = t & 63u;
-    px = blockIdx.x * kTile + (w & 1u) * 8u + (l & 7u);
-    py = blockIdx.y * kTile + (w >> 1) * 8u + (l >> 3);
+    const uint32_t w = threadIdx.x >> 6, l = threadIdx.x & 63u;
+    px = blockIdx.x * SW + (w % (SW / 8u)) * 8u + (l & 7u);
+    py = blockIdx.y * kTile + (w / (SW / 8u)) * 8u + (l >> 3);
     return px < W && py < H;
 }
 
-// Reuse passes gather from neighbours within the spatial radius: their
+dim3 tile_grid(uint32_t W, uint32_t H, uint32_t SW = (uint32_t)kTile)
+{
+    return dim3((W + SW - 1) / SW, (H + kTile - 1) / kTile);
+}
+
+// The spatial pass gathers from neighbours within its radius: its
 // workgroups are given tiles in XCD stripes, so that a pixel's neighbours
 // are mostly read through one XCD's L2.  Workgroup L runs on XCD L % 8 and
 // takes tile L / 8 (row-major) of stripe L % 8, a band of ceil(tx / 8) tile
-// columns.
-// Tiles of SW x 16 pixels, one of t's lanes each.
+// columns (tiles of SW x 16 pixels, one of t's lanes each).
 template <uint32_t SW>
 __device__ __forceinline__ bool tile_pixel_striped(uint32_t W, uint32_t H, uint32_t &px, uint32_t &py, uint32_t t)
 {
@@ -61,23 +70,6 @@ dim3 striped_grid(uint32_t W, uint32_t H, uint32_t SW)
     const uint32_t sw = (tx + kXcds - 1) / kXcds;
     return dim3(kXcds * sw * ty);
 }
-
-// the pixel of a lane of the passes of one thread per pixel: 16x16 tiles in
-// image order, wider ones in stripes
-template <uint32_t SW>
-__device__ __forceinline__ bool pass_pixel(uint32_t W, uint32_t H, uint32_t &px, uint32_t &py)
-{
-    if constexpr (SW == (uint32_t)kTile) return tile_pixel(W, H, px, py);
-    else return tile_pixel_striped<SW>(W, H, px, py, threadIdx.x);
-}
-
-dim3 tile_grid(uint32_t W, uint32_t H)
-{
-    uint32_t tx = (W + kTile - 1) / kTile, ty = (H + kTile - 1) / kTile;
-    return dim3(tx, ty);
-}
-
-dim3 pass_grid(uint32_t W, uint32_t H, uint32_t SW) { return SW == (uint32_t)kTile ? tile_grid(W, H) : striped_grid(W, H, SW); }
 
 struct GB {
     V3 pos;
@@ -1214,7 +1206,7 @@ __global__ void __launch_bounds__(SW * kTile, SW == 16u ? 8 : 6)
 {
     using Acc = typename std::conditional<SW != (uint32_t)kTile, GeoSmall, typename std::conditional<LDS, GeoLds, GeoGlobal>::type>::type;
     uint32_t px, py;
-    const bool inside = pass_pixel<SW>(gb.width, gb.height, px, py);
+    const bool inside = tile_pixel<SW>(gb.width, gb.height, px, py);
     if constexpr (SW != (uint32_t)kTile) {
         stage_small(sc);
         __syncthreads();
@@ -1594,7 +1586,7 @@ __global__ void __launch_bounds__(SW * kTile, GLOSSY ? 1 : SW == 16u ? 5 : 6)
 {
     using Acc = typename std::conditional<SW != (uint32_t)kTile, GeoSmall, typename std::conditional<LDS, GeoLds, GeoGlobal>::type>::type;
     uint32_t px, py;
-    const bool inside = pass_pixel<SW>(gb.width, gb.height, px, py);
+    const bool inside = tile_pixel<SW>(gb.width, gb.height, px, py);
     if constexpr (SW != (uint32_t)kTile) {
         stage_small(sc);
         __syncthreads();
@@ -2293,7 +2285,7 @@ gi_status gi_resample_temporal(const gi_scene *scene, const gi_gbuffer *gb, cons
     }
     const SceneTiles st(scene);
 #define GI_TP(L, G, SW)                                                                                        \
-    k_temporal<L, G, SW><<<pass_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(*scene, *gb, *gb_prev, *prev_cam, *cur_in, \
+    k_temporal<L, G, SW><<<tile_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(*scene, *gb, *gb_prev, *prev_cam, *cur_in, \
                                                                                     *history, *params, m_hist_cap, *out, seed, frame)
     if (glossy_scene(scene)) {
         if (st.lds) GI_TP(true, true, 16u); else GI_TP(false, true, 16u);
@@ -2349,7 +2341,7 @@ gi_status gi_shade(const gi_scene *scene, const gi_gbuffer *gb, const gi_probes 
     float4 *img = reinterpret_cast<float4 *>(out_rgba);
     const bool f16 = probes->texel == GI_TEXEL_F16;
 #define GI_SH(L, G, T, SW)                                                                                     \
-    k_shade<L, false, G, T, SW><<<pass_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(                    \
+    k_shade<L, false, G, T, SW><<<tile_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(                    \
         *scene, *gb, *probes, *res, rs, *params, img, nullptr, gi_mlp{}, seed, frame)
     if (glossy) {
         if (st.lds) { if (f16) GI_SH(true, true, kTexF16, 16u); else GI_SH(true, true, kTexF32, 16u); }
@@ -2462,7 +2454,7 @@ gi_status gi_shade_mlp(const gi_scene *scene, const gi_gbuffer *gb, const gi_pro
         const float4 *rs = reinterpret_cast<const float4 *>(resid);
         float4 *img = reinterpret_cast<float4 *>(out_rgba);
 #define GI_SH(L, SW)                                                                                   \
-    k_shade<L, true, false, kTexAny, SW><<<pass_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(      \
+    k_shade<L, true, false, kTexAny, SW><<<tile_grid(W, H, SW), SW * kTile, st.lds, S(stream)>>>(      \
         *scene, *gb, *probes, *res, rs, *params, img, q, *mlp, 0ull, 0u)
         if (st.wide) GI_SH(true, 48u);
         else if (st.lds) GI_SH(true, 16u);
