@@ -53,7 +53,13 @@ __device__ __forceinline__ V3 ld3(const float *a) { return v3(a[0], a[1], a[2]);
 // words 0 and 2 by the two round constants, crosses the high halves (xored
 // with the neighbour word and the key) and the low halves; the key advances
 // by the two Weyl constants between rounds.
+// XOR3: the two xors of a word as one instruction, for kernels bound by vector
+// issue (k_initial_tile 2% faster, k_spatial at k = 8 1-3%, k_temporal_small
+// 2%).  It keeps the first rounds' uniform words out of scalar registers, so
+// kernels bound by a walk's latency lose by it: k_cand from global memory 2%,
+// k_temporal and k_initial 1%.
 // --------------------------------------------------------------------------
+template <bool XOR3 = false>
 __device__ __forceinline__ uint4 philox(uint64_t seed, uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3)
 {
     uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
@@ -63,7 +69,8 @@ __device__ __forceinline__ uint4 philox(uint64_t seed, uint32_t c0, uint32_t c1,
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
         uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
         uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-        uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96), n2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
+        uint32_t n0 = XOR3 ? __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96) : hi1 ^ c1 ^ k0;
+        uint32_t n2 = XOR3 ? __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96) : hi0 ^ c3 ^ k1;
         c0 = n0;
         c1 = lo1;
         c2 = n2;

@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(kProbeBlock, LDS || GLOSSY ? 5 : 7)
     const uint32_t R = pp.rays;
     bool odd = false;                     // a squared distance or radiance that is no finite number
     for (uint32_t r = threadIdx.x; r < R; r += kProbeBlock) {
-        uint4 rn = philox(seed, pi, frame, kPassProbe, r);
+        uint4 rn = philox<true>(seed, pi, frame, kPassProbe, r);
         V3 w = sphere_dir(u01(rn.x), u01(rn.y));
         Hit h;
         V3 L;
@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(kProbeBlock, LDS || GLOSSY ? 5 : 7)
                 L = v3(fmaf(alb.x, q.x, emit.x), fmaf(alb.y, q.y, emit.y), fmaf(alb.z, q.z, emit.z));
             }
             if (GLOSSY && ks > 0.0f) {
-                const uint4 rg = philox(seed, pi, frame, kPassGlossyProbe, r);
+                const uint4 rg = philox<true>(seed, pi, frame, kPassGlossyProbe, r);
                 L = L + glossy_term<kTexOf<F16>>(in, view_bias(hp, P, in.bias_dist), n, -w, ks, ra, u01(rg.x), u01(rg.y));
             }
             dist = fminf(h.t, in.d_max);
@@ -872,7 +872,7 @@ __global__ void __launch_bounds__(NT, 4)
                 word[e] = ~0u;
                 continue;
             }
-            const uint4 rn = philox(seed, p_own, frame, kPassInitial, i);
+            const uint4 rn = philox<true>(seed, p_own, frame, kPassInitial, i);
             V3 w;
             bool ok = true;
             if (GLOSSY && pg > 0.0f && u01(rn.w) < pg) ok = ggx_sample(own.n, own.wo, own.rough, u01(rn.x), u01(rn.y), w);
@@ -904,7 +904,7 @@ __global__ void __launch_bounds__(NT, 4)
                 g = load_gb<GLOSSY>(gb, p);
             }
             const V3 o = madd(g.pos, sc.eps, g.n);
-            const uint4 rn = philox(seed, p, frame, kPassInitial, i);
+            const uint4 rn = philox<true>(seed, p, frame, kPassInitial, i);
             V3 w, y = v3(0.0f, 0.0f, 0.0f), ny = y, L = y, res0 = y;
             float phat = 0.0f, wi = 0.0f;
             uint32_t prim = GI_MISS;
@@ -928,7 +928,7 @@ __global__ void __launch_bounds__(NT, 4)
                 const float cx = dot(g.n, wv), cy = -dot(ny, wv);
                 if (cx > 0.0f && cy > 0.0f) {
                     if constexpr (GLOSSY) {
-                        const uint4 rg = philox(seed, p, frame, kPassGlossyCand, i);
+                        const uint4 rg = philox<true>(seed, p, frame, kPassGlossyCand, i);
                         L = radiance_toward_g<TEX>(sc, pr, prim, y, ny, g.pos, u01(rg.x), u01(rg.y));
                         const V3 f = bsdf(g.alb, g.ks, g.rough, g.n, g.wo, wv) * L;
                         const float G = cx * cy * rcp(d2);
@@ -979,7 +979,7 @@ __global__ void __launch_bounds__(NT, 4)
             for (uint32_t i = base; i < end; ++i) {
                 const float wi = __uint_as_float(word[((i - base) << (lw + lh)) + t]);
                 wsum += wi;
-                if (u01(philox(seed, p_own, frame, kPassInitial, i).z) * wsum < wi) chosen = i;
+                if (u01(philox<true>(seed, p_own, frame, kPassInitial, i).z) * wsum < wi) chosen = i;
             }
             sum[t] = wsum;
             if (base + C >= M && chosen == ~0u) {
@@ -1051,7 +1051,7 @@ __global__ void __launch_bounds__(kTileBlock, 4)
             const uint32_t i = base + (((uint32_t)j * kTileBlock + t) >> (lw + lh));
             at[j] = ~0u;
             if (!on || i >= M) continue;
-            const uint4 rn = philox(seed, p, frame, kPassInitial, i);
+            const uint4 rn = philox<true>(seed, p, frame, kPassInitial, i);
             w[j] = cosine_dir(nrm, u01(rn.x), u01(rn.y));
             const uint32_t b = sort_bin_of(w[j]) >> 2;
             at[j] = b | (atomicAdd(&hist[b], 1u) << 16);
@@ -1282,7 +1282,7 @@ __global__ void __launch_bounds__(128)
             if (similar(g, gq, pp)) {
                 const Res rh = load_res(hist, (uint32_t)q);
                 M1 = min(rh.M, m_hist_cap);
-                const uint4 rn = philox(seed, p, frame, kPassTemporal, 0u);
+                const uint4 rn = philox<true>(seed, p, frame, kPassTemporal, 0u);
                 merge_in<false>(m, g, rh, M1, u01(rn.x), pp.g_max);
                 qprev = (uint32_t)q;
             }
@@ -1412,7 +1412,7 @@ __global__ void __launch_bounds__(SW == 8u ? 256u : SW * kTile, SW == 48u ? 6 : 
             drawn[j] = false;
             uq[j] = 0.0f;
             if ((uint32_t)j >= pp.k) continue;
-            const uint4 rn = philox(seed, p, frame, kPassSpatial0 + pass, (uint32_t)j);
+            const uint4 rn = philox<true>(seed, p, frame, kPassSpatial0 + pass, (uint32_t)j);
             const float rad = pp.radius * fsqrt(u01(rn.x));
             const float s_ = sin_rev(u01(rn.y)), c_ = cos_rev(u01(rn.y));
             const int qx = (int)px + (int)floorf(rad * c_ + 0.5f);
