@@ -1983,18 +1983,25 @@ bool tile_form(const gi_scene *sc, const gi_params *pp, uint32_t W, uint32_t H)
 constexpr uint64_t kSmallImage = 65536u;
 
 // Where the learned-cache form traces its candidates by tiles.  The walks it
-// replaces cost less than the probe form's pixels, so fewer frames gain: with
-// 256 primitives from M = 8 on (1920x1080: M = 32 5.69 -> 4.46 ms, M = 13
-// 2.33 -> 1.97, M = 8 1.47 -> 1.26, whole pass; 64x36, M = 32: 765 -> 234 us;
-// M = 4 0.81 -> 0.84); with 1024 the lists are longer and leave room for half
-// the rays per round, and of large images only M = 32 gains (1920x1080 8.31 ->
-// 7.91 ms; M = 13 3.38 -> 3.72); of small ones, which the pixel form does not
-// spread over the chip, all do (238x121, M = 13: 556 -> 337 us; 320x200, M = 8:
-// 362 -> 300; 64x36, M = 8: 321 -> 215).
+// replaces cost less than the probe form's pixels, so fewer frames gain: up to
+// 512 primitives from M = 8 on (256 primitives, 1920x1080: M = 32 5.69 -> 4.46
+// ms, M = 13 2.33 -> 1.97, M = 8 1.47 -> 1.26, whole pass; 64x36, M = 32: 765
+// -> 234 us; M = 4 0.81 -> 0.84).  Longer lists leave room for half the rays
+// per round.  Small images, which the pixel form does not spread over the
+// chip, gain all the same (1024 primitives: 238x121, M = 13: 556 -> 337 us;
+// 320x200, M = 8: 362 -> 300; 64x36, M = 8: 321 -> 215), larger ones only from
+// M = 24 on (1283x721, 1024 primitives: M = 24 2.97 -> 2.97 ms, M = 32 3.94 ->
+// 3.55), and the largest later the more primitives there are (1920x1080 and
+// 2560x1440: 600 primitives, M = 24 6.24 -> 5.89 and 10.81 -> 10.98 ms, M = 26
+// 11.71 -> 11.60; 1024, M = 24 6.04 -> 6.24 and 10.6 -> 11.5, M = 30 7.60 ->
+// 7.14 and 13.31 -> 13.25).
 bool cand_tiles(const gi_scene *sc, const gi_params &pp, uint32_t W, uint32_t H)
 {
-    if (sc->n_prims > kListMaxPrims || (sc->options & GI_OPT_NO_LDS) != 0u) return false;
-    return pp.M >= (sc->n_prims > 512u && (uint64_t)W * H > kSmallImage ? 24u : 8u);
+    const uint32_t n = sc->n_prims;
+    if (n > kListMaxPrims || (sc->options & GI_OPT_NO_LDS) != 0u) return false;
+    const uint64_t px = (uint64_t)W * H;
+    if (n <= 512u || px <= kSmallImage) return pp.M >= 8u;
+    return pp.M >= 24u + (px > 1500000u ? 6u * (n - 512u) / 512u : 0u);
 }
 
 bool glossy_scene(const gi_scene *sc) { return (sc->options & GI_OPT_GLOSSY) != 0u; }
