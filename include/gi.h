@@ -269,7 +269,10 @@ gi_status gi_probe_update(const gi_scene *scene, const gi_probes *in, gi_probes 
 /* Probe query Q(p, n) = E(p, n)/pi (Eq. 4; probe weights of the DDGI volume
  * the paper builds on, with the probes' mean visibility of Sec. 3.2):
  * trilinear x backface x Chebyshev-visibility blend of the 8 probes of p's
- * cell, normalised.  p, nrm: n points as 3 floats each; out: 3 floats each. */
+ * cell, normalised.  p, nrm: n points as 3 floats each; out: 3 floats each.
+ * (Texels are meant to be finite.  A probe of weight zero that holds one that
+ * is not makes this query's result not finite either; the passes that query
+ * the volume at their hits may leave such a probe out.) */
 gi_status gi_probe_query(const gi_probes *probes, uint32_t n, const float *p, const float *nrm,
                          float *out, void *stream);
 

@@ -776,10 +776,11 @@ __device__ __forceinline__ void irr_record(__amdgpu_buffer_rsrc_t r, uint32_t of
 // Per-axis quantities of the query cell's two corner layers: offsets from the
 // layers' probe coordinate to p, the trilinear fraction toward the upper
 // layer, and the cell's lower probe index.  (pv - lo) / sp is rounded as the
-// IEEE division rounds it: r = 1/sp correctly rounded is the same for every
-// query (formed once per thread), and two residual steps from a * r give the
-// correctly rounded quotient in 5 instructions instead of the 11 of the
-// division.
+// IEEE division rounds it, by Markstein's residual correction: r = 1/sp
+// correctly rounded is the same for every query (formed once per thread), and
+// two residual steps from a * r give the correctly rounded quotient in 5
+// instructions instead of the 11 of the division.  That takes 1/sp and a * r
+// to be finite, as they are for a hit point.
 struct QueryAxis {
     float e0, e1, fr;
     uint32_t b;
@@ -844,7 +845,9 @@ __device__ __forceinline__ V3 probe_query_fmt(const gi_probes &pr, V3 p, V3 n)
         for (int oy = 0; oy < 2; ++oy) {
             const float ey = oy ? ay.e1 : ay.e0, ty = oy ? ay.fr : 1.0f - ay.fr;
             // a layer of weight zero (p beyond the outermost probes, as next to
-            // the walls of a room) adds nothing: its records are not read
+            // the walls of a room) adds nothing while its texels are finite: its
+            // records are not read (reading them costs 10%: 1920x1080, M = 32,
+            // 3.09 -> 3.40 ms; shading 210 -> 279 us)
             if (ty == 0.0f || tz == 0.0f) continue;
 #pragma unroll
             for (int ox = 0; ox < 2; ++ox) {

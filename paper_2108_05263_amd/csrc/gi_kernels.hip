@@ -440,11 +440,100 @@ __global__ void __launch_bounds__(kProbeBlock, LDS || GLOSSY ? 5 : 7)
     }
 }
 
+// Q at a caller's points: probe_query's blend and sums, bit for bit on finite
+// input, without the shortcuts that its callers' points allow.  The quotient
+// is a division, so that points beyond every bound land in the outermost
+// cell, and layers of weight zero are read, so that a texel that is no finite
+// number shows.  One corner pair per iteration, with both probes' records
+// loaded together, is also the faster form for points that are not sorted:
+// 4,000,000 random ones, 65,536 binary16 probes 0.99 ms, probe_query 1.14
+// (FP32 1.19 and 1.17).
+struct PointAxis {
+    float d0, d1, fr;
+    uint32_t base, step;
+};
+
+__device__ __forceinline__ PointAxis point_axis(float pv, float lo, float sp, int na, uint32_t stride)
+{
+    PointAxis q;
+    float g = (pv - lo) / sp - 0.5f;
+    g = fminf(fmaxf(g, 0.0f), (float)(na - 1));
+    const int b = min(max((int)floorf(g), 0), max(na - 2, 0));
+    q.fr = na >= 2 ? g - (float)b : 0.0f;
+    const int i1 = min(b + 1, na - 1);
+    q.d0 = lo + ((float)b + 0.5f) * sp - pv;
+    q.d1 = lo + ((float)i1 + 0.5f) * sp - pv;
+    q.base = (uint32_t)b * stride;
+    q.step = (uint32_t)(i1 - b) * stride;
+    return q;
+}
+
+template <bool kF16>
+__device__ __forceinline__ V3 point_query(const gi_probes &pr, V3 p, V3 n)
+{
+    using F = ProbeFmt<kF16>;
+    const int nx = (int)pr.dims[0], ny = (int)pr.dims[1], nz = (int)pr.dims[2];
+    const PointAxis ax = point_axis(p.x, pr.lo[0], pr.spacing[0], nx, 1u);
+    const PointAxis ay = point_axis(p.y, pr.lo[1], pr.spacing[1], ny, (uint32_t)nx);
+    const PointAxis az = point_axis(p.z, pr.lo[2], pr.spacing[2], nz, (uint32_t)(nx * ny));
+    const uint32_t base = ax.base + ay.base + az.base;
+    const Bilin bn = bilin(n, kIrrN);
+    const uint32_t np = (uint32_t)(nx * ny * nz);
+    const uint32_t irr_q = F::kIrrRec * (uint32_t)bn.q * np;   // slice of record q
+    const __amdgpu_buffer_rsrc_t dep_r = tex_rsrc(pr.dep, np * F::kDepProbe);
+    const __amdgpu_buffer_rsrc_t irr_r = tex_rsrc(pr.irr, np * (uint32_t)kIrrQuads * F::kIrrRec);
+    const float w00 = (1.0f - bn.ax) * (1.0f - bn.ay), w10 = bn.ax * (1.0f - bn.ay);
+    const float w01 = (1.0f - bn.ax) * bn.ay, w11 = bn.ax * bn.ay;
+    float sx = 0.0f, sy = 0.0f, sz = 0.0f, wsum = 0.0f;
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c) {
+        const bool oy = (c & 1) != 0, oz = (c & 2) != 0;
+        const float dy = oy ? ay.d1 : ay.d0, dz = oz ? az.d1 : az.d0;
+        const float ty = oy ? ay.fr : 1.0f - ay.fr, tz = oz ? az.fr : 1.0f - az.fr;
+        const uint32_t pyz = base + (oy ? ay.step : 0u) + (oz ? az.step : 0u);
+#pragma unroll
+        for (int ox = 0; ox < 2; ++ox) {
+            const V3 tp = v3(ox ? ax.d1 : ax.d0, dy, dz);
+            const float tx = ox ? ax.fr : 1.0f - ax.fr;
+            const uint32_t pi = pyz + (ox ? ax.step : 0u);
+            const float r2 = dot(tp, tp);
+            const bool at_probe = !(r2 > 0.0f);
+            const float ir = frsq(r2);
+            const float r = r2 * ir;
+            const float hh = 0.5f * (1.0f + dot(n, tp) * ir);
+            // depth moments toward p (a probe sitting exactly at p reads any texel, unused)
+            const V3 dv = at_probe ? v3(0.0f, 0.0f, 1.0f) : -tp;
+            const Bilin bd = bilin(dv, kDepN);
+            float2 d[4];
+            dep_record<kF16>(dep_r, __umul24(pi, F::kDepProbe) + F::kDepRec * (uint32_t)bd.q, d);
+            float4 e0, e1, e2;
+            irr_record<kF16>(irr_r, irr_q + __umul24(pi, F::kIrrRec), e0, e1, e2);
+            const float v00 = (1.0f - bd.ax) * (1.0f - bd.ay), v10 = bd.ax * (1.0f - bd.ay);
+            const float v01 = (1.0f - bd.ax) * bd.ay, v11 = bd.ax * bd.ay;
+            const float mu = v00 * d[0].x + v10 * d[1].x + v01 * d[2].x + v11 * d[3].x;
+            const float mu2 = v00 * d[0].y + v10 * d[1].y + v01 * d[2].y + v11 * d[3].y;
+            const float var = fmaxf(fmaf(-mu, mu, mu2), pr.var_floor);
+            const float dd = r - mu;
+            const float cheb = var * rcp(fmaf(dd, dd, var));
+            const float vis = (!at_probe && r > mu) ? cheb * cheb * cheb : 1.0f;
+            const float back = at_probe ? 0.45f : hh * hh + 0.2f;
+            const float wgt = tx * ty * tz * fmaxf(back * vis, 1e-6f);
+            sx = fmaf(wgt, w00 * e0.x + w10 * e0.w + w01 * e1.z + w11 * e2.y, sx);
+            sy = fmaf(wgt, w00 * e0.y + w10 * e1.x + w01 * e1.w + w11 * e2.z, sy);
+            sz = fmaf(wgt, w00 * e0.z + w10 * e1.y + w01 * e2.x + w11 * e2.w, sz);
+            wsum += wgt;
+        }
+    }
+    const float iw = rcp(wsum);
+    return v3(iw * sx, iw * sy, iw * sz);
+}
+
 __global__ void k_probe_query(gi_probes pr, uint32_t n, const float *p, const float *nrm, float *out)
 {
     uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    V3 q = probe_query(pr, ld3(p + 3 * i), ld3(nrm + 3 * i));
+    const V3 a = ld3(p + 3 * i), b = ld3(nrm + 3 * i);
+    const V3 q = pr.texel == GI_TEXEL_F16 ? point_query<true>(pr, a, b) : point_query<false>(pr, a, b);
     out[3 * i] = q.x;
     out[3 * i + 1] = q.y;
     out[3 * i + 2] = q.z;
