@@ -334,8 +334,15 @@ __global__ void __launch_bounds__(kProbeBlock, LDS || GLOSSY ? 5 : 7)
             float c = nt.x * ry.x + nt.y * ry.y + nt.z * ry.z;
             if (kAll || c > 0.0f) {
                 if (kAll) c = fmaxf(c, 0.0f);
-                const float e = pp.sharpness * __log2f(c), d = ry.w;
-                const float w = kTiny ? exp2f(e) : __builtin_amdgcn_exp2f(e);
+                const float l = __log2f(c), e = pp.sharpness * l, d = ry.w;
+                float w;
+                if (kTiny) {
+                    // 2^e, a denormal one by way of e + 64 (rounded once)
+                    const bool low = e < -126.0f;
+                    w = __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(fmaf(pp.sharpness, l, low ? 64.0f : 0.0f)), low ? -64 : 0);
+                } else {
+                    w = __builtin_amdgcn_exp2f(e);
+                }
                 m1 = fmaf(w, d, m1);
                 m2 = fmaf(w, d * d, m2);
                 den += w;
