@@ -1394,7 +1394,7 @@ __global__ void __launch_bounds__(128)
             ph = res_target<false>(g, r, pp.g_max);
             r.W = 0.0f;
             ray = pp.unbiased && ph > 0.0f;
-            if (ray && M1 != 0u && res_target<false>(load_gb<false>(gbp, qprev), r, pp.g_max) > 0.0f) q1 = qprev;
+            if (ray && M1 != 0u && !(res_target<false>(load_gb<false>(gbp, qprev), r, pp.g_max) <= 0.0f)) q1 = qprev;
         }
         store_res(out, p, r);
     };

@@ -66,7 +66,7 @@ def test_large_temporal_pass(room, W, H, lds, open_, kw):
     ("tiny", 256, 256, False, 1, "f32"), ("hd", 250, 141, False, 1, "f32"), ("hd", 101, 77, True, 0, "f16"),
     ("uhd", 255, 257, False, 1, "f32"), ("uhd", 250, 141, True, 1, "f16"), ("uhd", 99, 101, False, 0, "f32"),
 ])
-def test_small_temporal_tiles_are_the_large_ones(room, W, H, open_, unbiased, gb_format):
+def test_small_temporal_tiles_are_the_large_ones(room, W, H, open_, unbiased, gb_format, odd=False):
     from paper_2108_05263_amd import gi
     cfg = sg.CONFIGS[room]
     cfg = dataclasses.replace(cfg, probe_dims=(4, 4, 4), probe_spacing=cfg.room_hi[0] / 4,
@@ -84,6 +84,9 @@ def test_small_temporal_tiles_are_the_large_ones(room, W, H, open_, unbiased, gb
         gi.trace_gbuffer(big.dscene, cam, big.gb[f])
         gi.resample_initial(big.dscene, big.gb[f], big.probe, big.params, big.res[f], big.resid, 5, f)
     big.gb[0].pos_depth[::5, 3] *= 1.5        # a previous vertex that the depth test refuses
+    if odd:
+        big.gb[0].albedo[::7, 1] = float("nan")
+        big.gb[0].pos_depth[3::11, 1] = float("inf")
     for f in (0, 1):
         for a, b in ((small.gb[f], big.gb[f]), (small.res[f], big.res[f])):
             for name, t in vars(a).items():
@@ -101,3 +104,9 @@ def test_small_temporal_tiles_are_the_large_ones(room, W, H, open_, unbiased, gb
     assert 0.7 < merged < 0.9, "four of five pixels take over their history"
     for a, b in zip(*out):
         assert torch.equal(a, b), f"{int((a != b).sum())} words differ"
+
+
+# previous vertices that are no numbers: a target that is none counts as support in every form
+@pytest.mark.parametrize("room,W,H", [("hd", 250, 141), ("uhd", 99, 101)])
+def test_previous_vertices_of_no_number(room, W, H):
+    test_small_temporal_tiles_are_the_large_ones(room, W, H, False, 1, "f32", odd=True)
