@@ -939,7 +939,7 @@ __global__ void __launch_bounds__(NT, 4)
         // 3840x2160, 1024 primitives: 21.4 ms, with `on` 21.9; the glossy ones
         // more: 1920x1080 5.29 ms with `on`, 5.35 without)
         const V3 at = list_origin(org);
-        block_boxes<NT>(at, list_axis(own.n), GLOSSY ? on : on && at.x < kInf, reinterpret_cast<float4 *>(word), ob, nb);
+        block_boxes<NT>(at, list_axis(org, own.n), GLOSSY ? on : on && at.x < kInf, reinterpret_cast<float4 *>(word), ob, nb);
         if (__syncthreads_or(on) == 0) return;             // no pixel of the tile is active
         build_lists<NT>(sc, lists, ob, nb, word);          // in the rays' space
     }
@@ -1127,7 +1127,7 @@ __global__ void __launch_bounds__(kTileBlock, 4)
     }
     {
         Box3 ob, nb;
-        block_boxes<kTileBlock>(list_origin(org), list_axis(nrm), on, reinterpret_cast<float4 *>(ray), ob, nb);
+        block_boxes<kTileBlock>(list_origin(org), list_axis(org, nrm), on, reinterpret_cast<float4 *>(ray), ob, nb);
         if (__syncthreads_or(on) != 0) build_lists<kTileBlock>(sc, lists, ob, nb, reinterpret_cast<uint32_t *>(ray));
     }
     if (t < TP) {

@@ -85,3 +85,17 @@ def test_odd_pixels_find_the_brute_force_hits(open_, form):
     lists, brute = (_planes(form, scene, 90, 50, 32, lds, _odd_pixels) for lds in (True, False))
     for a, b in zip(lists, brute):
         assert torch.equal(a, b), f"{int((a != b).sum())} words differ"
+
+
+@pytest.mark.parametrize("form", ["probe", "cache"])
+@pytest.mark.parametrize("W,H,M", [(90, 50, 32), (320, 330, 24), (61, 77, 8)])
+@pytest.mark.parametrize("values", [(float("nan"), float("inf"), -float("inf")), (3e38, -3e38), (1e19, -1e17)])
+def test_scattered_pixels_without_a_place(W, H, M, form, values):
+    """One pixel in seven far off, further than FP32 can span, or not a point, along one axis."""
+    def edit(gb):
+        i = torch.arange(0, gb.pos_depth.shape[0], 7, device="cuda")
+        gb.pos_depth[i, 1] = torch.tensor(values, device="cuda")[torch.arange(len(i), device="cuda") % len(values)]
+
+    lists, brute = (_planes(form, sg.make_scene(CFG), W, H, M, lds, edit) for lds in (True, False))
+    for a, b in zip(lists, brute):
+        assert torch.equal(a, b), f"{int((a != b).sum())} words differ"
