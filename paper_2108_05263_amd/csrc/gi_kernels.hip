@@ -791,14 +791,17 @@ __global__ void __launch_bounds__(kBlock, 4)
 // writes the reservoirs.  Every candidate goes through the arithmetic of
 // k_initial and the weights are summed in its order, so the results are those
 // of k_initial bit for bit.
-// Bound by vector-ALU issue (86% of its cycles at 1920x1080, M = 32) and as
-// much by the L1's return path (85%: the five 16-byte loads of a probe take
-// about 35 cycles each, one per distinct line of four lanes).  Against the
-// pixel form, M = 32: 250x141 0.795 -> 0.226 ms, 1920x1080 5.96 -> 3.23 ms,
-// with glossy layers and binary16 records 7.63 -> 5.04 ms, 3840x2160 with
-// 1024 primitives 42.7 -> 19.7 ms.  512 threads and up to 80 KB let two
-// workgroups share a CU, one tracing while the other sorts (one workgroup of
-// 1024 threads: 4.7 ms against 3.9 at 1920x1080).
+// Bound by vector-ALU issue (0.87 of the peak at 1920x1080, M = 32) and as
+// much by the L1's return path (0.85: the five 16-byte loads of a probe take
+// about 35 cycles each, one per distinct line of four lanes).  Some of the
+// issue is register traffic: the thread's own pixel lives across the trace, so
+// 23 VGPRs (96 B a lane) and 75 scalars spill, 60 and 114 in the glossy forms,
+// and a 1920x1080 launch writes 643 MB for 141 MB of output.  Against the
+// pixel form, M = 32: 250x141 0.734 -> 0.218 ms, 1920x1080 5.77 -> 3.08 ms,
+// with glossy layers 8.86 -> 5.20 ms, 3840x2160 with 1024 primitives 46.5 ->
+// 21.3 ms.  512 threads and up to 80 KB let two workgroups share a CU, one
+// tracing while the other sorts (one workgroup of 1024 threads: 4.7 ms against
+// 3.9 at 1920x1080, when that was chosen).
 constexpr int kTileBlock = 512;
 constexpr uint32_t kTileLds = 80u * 1024u;                // LDS of a workgroup: two share a CU
 constexpr uint32_t kSortBins = 4u * kBins;
@@ -1233,7 +1236,6 @@ __device__ __forceinline__ void merge_in(Merge &m, const GB &g, const Res &q, ui
     }
 }
 
-constexpr int kMaxDom = GI_MAX_K + 1;
 
 // Normalise the merged reservoir.  Domain slot j holds M_j (0 = slot unused:
 // a neighbour that was rejected or never drawn) and is loaded by dom(j);
@@ -1340,9 +1342,9 @@ __global__ void __launch_bounds__(SW * kTile, SW == 16u ? 8 : 6)
 // The temporal pass of an image of few pixels: an 8x8 tile's two rays per
 // pixel go to a wave each instead of one after the other, and the tiles to four
 // times as many CUs.  Bound by the latency of one walk; k_temporal -> this:
-// 64x64, 8 primitives 27 -> 16 us; 99x50, 256 primitives 62 -> 34; 320x180
-// 65 -> 34, 1024 primitives 79 -> 54.  (The second ray is cast whether or not
-// x sees the sample; W is zero if it does not.)
+// 64x64, 8 primitives 28 -> 17 us, 256 53 -> 29, 1024 93 -> 48; 320x200 27 ->
+// 17, 56 -> 32, 94 -> 50.  (The second ray is cast whether or not x sees the
+// sample; W is zero if it does not.)
 template <bool LDS>
 __global__ void __launch_bounds__(128)
     k_temporal_small(gi_scene sc, gi_gbuffer gb, gi_gbuffer gbp, gi_camera cam_prev, gi_reservoirs cur,
@@ -1435,18 +1437,6 @@ struct RayPool {
     uint16_t order[(KM + 1) * NT];
 };
 
-// Neighbour slots are static (KM of them, KM >= k): a slot that draws no
-// pixel (off-screen, the pixel itself, j >= k) points at the pixel itself,
-// so every neighbour load is in bounds and unconditional, and the loads of
-// all slots can be in flight together instead of one neighbour after the
-// other.
-// The visibility rays of all pixels go into one pool, sorted by direction
-// (about 5 per pixel at k = 5): cast pixel by pixel they kept 24 of a wave's
-// 64 lanes busy.  They are two thirds of the pass and bound it by vector-ALU
-// issue; 0.86 -> 0.59 ms at 1920x1080, 5.86 -> 2.87 ms at 3840x2160 (k = 5).
-// The rays that only decide Z are cast whether or not x sees the sample; W is
-// zero if it does not.  74 VGPRs, 5 waves per SIMD (4 with glossy layers, 6
-// for the 768-thread tiles).
 // The pixel of slot k of a tile: 8x8 pixels for 256 threads (SW = 8, tiles in
 // image order), else SW x 16 in stripes.
 template <uint32_t SW>
@@ -1462,6 +1452,22 @@ __device__ __forceinline__ bool spatial_pixel(uint32_t W, uint32_t H, uint32_t &
     }
 }
 
+// Neighbour slots are static (KM of them, KM >= k): a slot that draws no
+// pixel (off-screen, the pixel itself, j >= k) points at the pixel itself,
+// so every neighbour load is in bounds and unconditional, and the loads of
+// all slots can be in flight together instead of one neighbour after the
+// other.
+// The visibility rays of all pixels go into one pool, sorted by direction
+// (about 5 per pixel at k = 5): cast pixel by pixel they kept 24 of a wave's
+// 64 lanes busy, pooled 42.  The pass took 0.74 of the vector-issue peak
+// before the pool and takes 0.61 with it: as much as by issue it is bound by
+// the gathers of the pooled rays, which read their pixel's sample and their
+// domain's vertex again (104 M L2 requests, 78 M before).  0.776 -> 0.617 ms
+// at 1920x1080, 6.46 -> 3.03 ms at 3840x2160 with 1024 primitives (k = 5).
+// The rays that only decide Z are cast whether or not x sees the sample; W is
+// zero if it does not.  Waves per SIMD: 5 (74 VGPRs at k <= 5; k <= 8 takes
+// 96 and spills 3), 4 with glossy layers, 6 for the 768-thread tiles (k <= 8
+// there spills 17, with glossy layers 46).
 template <bool LDS, bool GLOSSY, int KM, uint32_t SW>
 __global__ void __launch_bounds__(SW == 8u ? 256u : SW * kTile, SW == 48u ? 6 : GLOSSY ? 4 : 5)
     k_spatial(gi_scene sc, gi_gbuffer gb, gi_reservoirs in, gi_params pp, uint32_t pass, gi_reservoirs out,
@@ -2066,7 +2072,11 @@ void launch_initial(bool light, bool glossy, bool f16, uint32_t lds, dim3 grid, 
 // 1.13x at 1280x720, 1.19x at 1920x1080), and for small ones, where the pixel
 // form leaves most of the chip idle (M = 8: 1.2-1.6x up to 320x180), unless
 // the primitives outnumber a small tile's rays; in between it does not
-// (640x360: M = 8 0.75x, M = 13 0.91x), nor below M = 8.
+// (640x360: M = 8 0.75x, M = 13 0.91x), nor below M = 8.  The line for large
+// images holds for other numbers of primitives too: 8 primitives, 1283x721, M
+// = 8 453 -> 302 us; 1024, 1283x721, M = 8 1.58 -> 1.29 ms, M = 13 2.55 ->
+// 1.92; 1920x1080, M = 8 3.26 -> 2.16 ms, M = 13 5.24 -> 3.12, M = 23 9.20 ->
+// 4.93.
 bool tile_form(const gi_scene *sc, const gi_params *pp, uint32_t W, uint32_t H)
 {
     if (pp->M_light > 0u || sc->n_prims > kListMaxPrims || (sc->options & GI_OPT_NO_LDS) || pp->M < 8u) return false;
@@ -2114,8 +2124,8 @@ void launch_initial_tile(const gi_scene *sc, const gi_gbuffer &gb, const gi_prob
     // two workgroups per CU), down to 8x8 pixels and, for images that would
     // not reach every CU with those, 4x4: large tiles sort more rays together
     // and cull the scene less often, but their primitive lists are longer.
-    // 1920x1080, M = 32: 16x16 3.62 ms, 32x16 3.95, 16x8 4.35, 8x8 5.80;
-    // 3840x2160: 32x16 23.4 ms, 16x16 24.5, 16x8 29.0.
+    // 1920x1080, M = 32, when this was chosen: 16x16 3.62 ms, 32x16 3.95, 16x8
+    // 4.35, 8x8 5.80; 3840x2160: 32x16 23.4 ms, 16x16 24.5, 16x8 29.0.
     const auto tiles = [&](uint32_t a, uint32_t b) {
         return (uint64_t)((W + (1u << a) - 1u) >> a) * ((H + (1u << b) - 1u) >> b);
     };
@@ -2191,11 +2201,12 @@ void launch_initial_probe(const gi_scene *sc, const gi_gbuffer &gb, const gi_pro
 // How the passes of one thread per pixel (temporal, shade) hold the scene: in
 // LDS for each 16x16 tile where four of them fit a CU; a larger one, in its
 // small form, shared by the 768 threads of a 48x16 tile, two of which fill a
-// CU; else in global memory.  3840x2160, 1024 primitives, global memory ->
-// wide tiles: shade 1.45 -> 1.06 ms, temporal 1.49 -> 1.37; 640x360: 81 -> 57
-// us, 125 -> 86.  (The small form in 16x16 tiles, 1920x1080, 256 primitives:
-// shade 232 us against 224, temporal 247 against 240.)  Glossy layers keep to
-// the first and the last: their walks hold too many registers for 768 threads.
+// CU; else in global memory.  1024 primitives, global memory -> wide tiles:
+// 3840x2160 shade 1.95 -> 1.25 ms, temporal 1.71 -> 1.55; 640x360 89 -> 62 us,
+// 119 -> 102; 40x2000 61 -> 45 us, 80 -> 65.  (The small form in 16x16 tiles,
+// 1920x1080, 256 primitives: shade 232 us against 224, temporal 247 against
+// 240.)  Glossy layers keep to the first and the last: their walks hold too
+// many registers for 768 threads.
 struct SceneTiles {
     uint32_t lds;
     bool wide;
@@ -2225,10 +2236,10 @@ void launch_spatial_t(const gi_scene *sc, uint32_t lds, uint32_t W, uint32_t H, 
 }
 
 // The scene in LDS where that leaves four workgroups of 256 threads on a CU
-// (1920x1080, 256 primitives: 0.59 ms, from global memory 0.88); a larger one
-// is shared by the 768 threads of a 48x16 tile, two of which fill a CU
-// (3840x2160, 1024 primitives: 2.87 ms, from global memory 3.76, shared by
-// 256 threads 5.18, by 512 3.85).
+// (1920x1080, 256 primitives, when this was chosen: 0.59 ms, from global
+// memory 0.88); a larger one is shared by the 768 threads of a 48x16 tile, two
+// of which fill a CU (3840x2160, 1024 primitives: 2.87 ms, from global memory
+// 3.76, shared by 256 threads 5.18, by 512 3.85).
 //
 // An image of few pixels leaves most of the chip idle, and six rays in a row
 // per thread are its time: tiles of 8x8 pixels share their rays between 256
@@ -2237,7 +2248,6 @@ void launch_spatial_t(const gi_scene *sc, uint32_t lds, uint32_t W, uint32_t H, 
 // 320x180: 41 -> 22, 57 -> 43, 74 -> 64; from 480x270 on the waves without
 // pixels cost as much as they gain (44 -> 46, 91 -> 77, 97 -> 85; 640x360: 56
 // -> 60, 114 -> 108, 133 -> 130).
-
 template <int KM, class... A>
 void launch_spatial(const gi_scene *sc, uint32_t W, uint32_t H, hipStream_t st, A... a)
 {

@@ -85,10 +85,10 @@ struct Box3 {
 // that the lists' distances are lowered by.  A pixel without either shows in
 // the normals' box, by a normal of kNoUnit or kNoPlace along x.  For directions
 // of other lengths no word lies beyond a hit (what the cells leave out still
-// lies off the ray); for an origin that is no point, or beyond kOrgFar,
-// every cell lists every primitive.  Such a pixel's rays find
-// what the brute-force loop finds.  (One component says it all: with three the
-// glossy FP32 form spills 17 more scalars, 1920x1080 5.41 ms against 5.31.)
+// lies off the ray); for an origin that is no point, or beyond kOrgFar, every
+// cell lists every primitive.  Such a pixel's rays find what the brute-force
+// loop finds.  (One component says it all: with three the glossy FP32 form
+// spills 17 more scalars, 1920x1080 5.41 ms against 5.31.)
 //
 // kOrgFar: up to here an empty slot's bounds stay finite beside its radius of
 // -inf (the tangent plane's normal below 2e22 before it cancels, times the

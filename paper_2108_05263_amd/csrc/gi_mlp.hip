@@ -11,9 +11,10 @@
 //
 // Training (2^14..2^16 samples per step, ~0.6 GFLOP) runs on the matrix cores
 // as well: one workgroup per 64 samples computes the forward pass, the loss
-// gradient, the backward pass and its partial weight gradient; two more
-// kernels sum the partials in a fixed order (groups of 16 workgroups, then
-// the groups), so the result does not depend on scheduling.
+// gradient, the backward pass and its partial weight gradient; one more
+// kernel sums the partials in a fixed order (groups of 16 workgroups, then
+// the groups), so the result does not depend on scheduling, and takes the
+// optimiser step.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -670,9 +671,6 @@ k_mlp_infer_fp8(gi_mlp m, uint32_t n, const float4 *pos, const float4 *nrm, floa
     }
 }
 
-// --------------------------------------------------------------------------
-// training
-// --------------------------------------------------------------------------
 // --------------------------------------------------------------------------
 // training on the matrix cores
 // --------------------------------------------------------------------------
