@@ -128,11 +128,12 @@ typedef struct gi_camera {
  *   emit stay float4; readers renormalise the half-precision normal.  Scenes
  *   must have fewer than 65535 - 6 primitives.
  * A pixel whose primary ray leaves the scene has prim = GI_MISS and emit = sky.
- * Normals are meant to be of unit length.  A normal of another length gives
- * the candidate rays formed about it directions of other lengths, which the
- * sphere test takes for unit ones: those rays find the closest hit of the
- * brute-force loop, or, where the initial pass walks the grid, one that may
- * depend on the grid's cells. */
+ * Positions are meant to be finite and normals of unit length.  A normal of
+ * another length gives the candidate rays formed about it directions of other
+ * lengths, which the sphere test takes for unit ones.  The rays of such a pixel,
+ * or of one without a finite position, find the closest hit of the brute-force
+ * loop, or, where the initial pass walks the grid, one that may depend on the
+ * grid's cells. */
 typedef struct gi_gbuffer {
     uint32_t width, height;
     float *pos_depth;
